@@ -24,6 +24,8 @@ A case is a dict of plain values:
   chunk   elements per chunk (stream, route, deliver)
   bf16    route: the mean gradient returns in BF16
 """
+import weakref
+
 import numpy as np
 import torch
 
@@ -197,9 +199,7 @@ class Context:
 
     def __init__(self, **kw):
         self.handle = sdp.sdp_ctx_create(0, **kw)
-
-    def __del__(self):
-        sdp.sdp_ctx_destroy(self.handle)
+        weakref.finalize(self, sdp.sdp_ctx_destroy, self.handle)
 
 
 def pinned(sample):

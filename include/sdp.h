@@ -48,8 +48,9 @@
  *  (the norm and c still come from the FP32 g_bar).
  *  A non-finite norm leaves every state and parameter unchanged.
  *  Results do not depend on the chunk size, on the mode (device or
- *  streamed) or on run-to-run scheduling: the norm is a fixed-order tree
- *  over fixed 4,096-element spans of each segment (sixteen per
+ *  streamed) or on run-to-run scheduling: the norm is a fixed-order sum over
+ *  fixed spans of each segment (256, 4,096 or 8,192 elements, by the number of
+ *  ranks and whether the pass stores g_bar; they divide the
  *  65,536-element tile, and chunks are whole tiles).  The host-update route
  *  with SDP_GBAR_F32 gives the same norm bits; its host cores evaluate the
  *  same FP64 expression, so its states agree with the other modes up to the
@@ -80,7 +81,7 @@ extern "C" {
 #define SDP_ERR_NONFINITE (-8)         /* gradient norm is NaN or Inf; nothing was updated */
 
 /* ---- constants --------------------------------------------------------- */
-#define SDP_NORM_TILE 65536 /* norm tile: the norm sums in a grid fixed per tile (sixteen partials each); chunk sizes are multiples of it */
+#define SDP_NORM_TILE 65536 /* norm tile: the norm sums in a grid fixed per tile; chunk sizes are multiples of it */
 #define SDP_MAX_RANKS 16    /* largest R */
 #define SDP_ALIGN 16        /* byte alignment required of every buffer */
 

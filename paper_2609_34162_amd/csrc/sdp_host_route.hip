@@ -282,7 +282,7 @@ int sdp_host_update_step(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, 
     int32_t R = 0;
     SDP_TRY(validate_segments(ctx, segs, n_segs, kAnyHost, kDeviceMem, false, &R));
     const Plan plan = make_plan(segs, n_segs);
-    SDP_TRY(ensure_partials(ctx, plan.tiles));
+    SDP_TRY(ensure_partials(ctx, plan.tiles * sdp::norm_pairs_per_tile(R, false)));
     SDP_TRY(ensure_host_stage(ctx));
     SDP_TRY(order_after_last(ctx, ctx->s_comp));
     SDP_TRY(order_after_last(ctx, ctx->s_copy));

@@ -20,10 +20,10 @@ struct NormState {
 };
 
 // One launch of the norm pass: `n` elements starting at a tile boundary of
-// a segment.  The grid is kNormSplit blocks per tile; block b covers the
-// elements [b*kNormSpan, min((b+1)*kNormSpan, n)) (none, past the end) and
-// writes the double-double pair partials[2b], partials[2b+1], so the tile k
-// of the launch owns pairs kNormSplit*k .. kNormSplit*k + kNormSplit - 1.
+// a segment.  The grid is norm_pairs_per_tile blocks per tile; block b covers
+// span b of the segment, kSpan elements (or fewer, or none past the end), and
+// writes the pair partials[2b], partials[2b+1], so the tile k of the launch
+// owns norm_pairs_per_tile pairs from that many times k.
 // When gbar_out is non-null it also stores g_bar there.
 struct NormArgs {
     const uint16_t *g[SDP_MAX_RANKS];
@@ -73,9 +73,35 @@ struct CopyBatch {
 };
 
 constexpr int kTile = SDP_NORM_TILE;
-constexpr int kNormSplit = 16;                   // norm blocks, and partial pairs, per tile
-constexpr int kNormSpan = kTile / kNormSplit;    // elements per norm block
-constexpr int kNormThreads = 256;
+// Shape of the norm pass for R ranks: spans of kSpan elements, one block of
+// kThreads per span, kVec elements per lane and load, kBatch groups of them
+// loaded before any is used.  (Rates: TB/s over 419M elements of normal
+// gradients, against about 7.1 for plain reads and 6.0 for plain writes.)
+//  - Storing g_bar for more than four ranks: the pass is bound by HBM's mix of
+//    R read streams and one write stream, which runs faster the closer together
+//    the accesses in flight lie: one-wave blocks of one group per lane reach
+//    6.58 at R = 8 (6.77 at R = 5, 6.21 at R = 16) where 256-thread blocks over
+//    4,096 elements reach 6.05-6.16 (5.83 at R = 16).
+//  - Reading alone: large blocks, whose one butterfly is spread over more
+//    elements (R = 8: 6.88 against 6.3-6.4 with one-wave blocks; R = 4: 6.79
+//    against 6.51).  One rank's 2 bytes per element leave the least time for
+//    arithmetic, so its lanes take 32 elements: 6.56, where 16 per lane reach
+//    5.5 and 8-byte loads 4.7.
+//  - Storing for up to four ranks (streamed mode, bound by the host link) keeps
+//    the reading shape's larger spans and so fewer partial pairs.
+template <int R, bool STORE>
+struct NormShape {
+    static constexpr bool kWaveBlocks = STORE && R > 4;
+    static constexpr int kThreads = kWaveBlocks ? 64 : 256;
+    static constexpr int kVec = R == 1 && !STORE ? 8 : 4;
+    static constexpr int kBatch = STORE ? 1 : R == 1 ? 4 : 2;
+    static constexpr int kSpan = kWaveBlocks ? 256 : R == 1 && !STORE ? 8192 : 4096;
+};
+// Partial pairs per norm tile (NormShape<R, store>::kSpan elements each).
+constexpr int norm_pairs_per_tile(int R, bool store) {
+    return kTile / (store ? (R > 4 ? NormShape<5, true>::kSpan : NormShape<1, true>::kSpan)
+                          : (R == 1 ? NormShape<1, false>::kSpan : NormShape<2, false>::kSpan));
+}
 constexpr int kFinalizeThreads = 1024;
 // More than kMergeRun span pairs are merged in two fixed stages: block b of
 // k_norm_merge merges pairs b*kMergeRun .. (b+1)*kMergeRun - 1 into pair b
@@ -90,10 +116,16 @@ constexpr int kUpdateThreads = 64;
 // the kernel does not use (the LDS of a compute unit divided by the cap, per
 // block).
 constexpr int kUpdateBlocksPerCU = 10;
-// The norm pass that stores g_bar (16 B read + 4 B written per element at
-// R = 8) is capped the same way at kNormStoreBlocksPerCU blocks of
-// kNormThreads; the plain norm pass, read only, runs uncapped.
-constexpr int kNormStoreBlocksPerCU = 4;
+// The norm pass that stores g_bar is capped the same way.  One-wave blocks
+// (more than four ranks): the fewer ranks, the more waves it takes to keep the
+// same bytes in flight.  Best caps measured: 24 at R = 5, 20 at 6 and 7, 15-16
+// at 8 and 9, 13-14 from 10 to 16; no cap costs 2-5%, half the best cap 20-30%.
+// 256-thread blocks: 4.  The read-only pass runs uncapped.
+constexpr int norm_store_blocks_per_cu(int R) {
+    return R > 4 ? (132 / R > 24 ? 24 : 132 / R < 14 ? 14 : 132 / R) : 4;
+}
+// Its static LDS per block (the block sum of waves 1..3).
+constexpr int norm_static_lds(int R, bool store) { return store && R > 4 ? 0 : (256 - 64) * 16; }
 constexpr int kVec = 8;     // elements per lane per access (16 B of BF16, 32 B of FP32)
 constexpr int kUpdVec = 4;  // fused update: elements per lane (8 B of BF16, 16 B of FP32)
 

@@ -56,14 +56,28 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     return bf16_rne(lo) | (bf16_rne(hi) << 16);
 }
 
+// fp32(fp64(s / R)) for a finite s.  R a power of two: the product by 1/R is
+// exact and equals s / R.  Else Markstein's correction: with y = fp64(1/R) and
+// q = fp64(s y), which is within one unit in the last place of s / R, the
+// remainder s - R q is exact in one fma and q + y (s - R q), rounded once, is
+// the correctly rounded quotient (no underflow here: a nonzero |s| is at
+// least 2^-133).  Three operations instead of the divide sequence's eleven.
+// (q only has to be finite: an infinite s takes mean_of_any.)
 template <int R>
 __device__ __forceinline__ float mean_of(double s) {
-    // R a power of two: the product by 1/R is exact and equals s / R.
+    constexpr double y = 1.0 / (double)R;
     if constexpr ((R & (R - 1)) == 0) {
-        return (float)(s * (1.0 / (double)R));
+        return (float)(s * y);
     } else {
-        return (float)(s / (double)R);
+        const double q = s * y;
+        return (float)__builtin_fma(__builtin_fma(-(double)R, q, s), y, q);
     }
+}
+
+// The same for any s, infinities and NaN included.
+template <int R>
+__device__ __forceinline__ float mean_of_any(double s) {
+    return (float)(s / (double)R);
 }
 
 // ---------------------------------------------------------------------------
@@ -168,7 +182,7 @@ __device__ __forceinline__ float mean_wide(const uint16_t *const *g, int64_t i) 
         if ((v & 0x7fffu) != 0) wide_add(w, v);
     }
     // NaN or an infinity: the IEEE result of the FP64 sum in rank order
-    if (!finite) return mean_of<R>(s);
+    if (!finite) return mean_of_any<R>(s);
     const bool neg = (w[kWideWords - 1] >> 31) != 0;
     if (neg) {
         uint32_t c = 1;
@@ -229,25 +243,49 @@ __device__ __forceinline__ float4 mean_wide_at4(const uint16_t *const *g, int64_
     return o;
 }
 
-// Fast route for the 2W elements held as BF16 in w[r][0..W-1] (two per word,
-// the lower half first).  Returns false if the values fail span_exact: the
-// caller must then take the wide route for them.
+// One or two ranks: FP32 gives the singly rounded mean by itself.  A BF16
+// value is an FP32 value (adding +0 turns -0 into the definition's +0), and
+// half of it is one too, so fma(a, 1/2, b/2) rounds (a + b) / 2 once; b/2
+// comes from an fma with +0, so that two zeros of any sign give +0.
+__device__ __forceinline__ float mean_fp32(float a) { return a + 0.0f; }
+__device__ __forceinline__ float mean_fp32(float a, float b) {
+    return __builtin_fmaf(a, 0.5f, __builtin_fmaf(b, 0.5f, 0.0f));
+}
+
+// The means of the 2W elements held as BF16 in w[r][0..W-1] (two per word,
+// the lower half first), by the fast route; for more than two ranks their
+// magnitudes are added to sp, and the means hold only if span_exact<R>(sp)
+// (else the caller takes the wide route).
+template <int R, int W>
+__device__ __forceinline__ void means_of(const uint32_t (&w)[R][W], float *g, Span &sp) {
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+        if constexpr (R == 1) {
+            g[2 * j] = mean_fp32(bf16_lo(w[0][j]));
+            g[2 * j + 1] = mean_fp32(bf16_hi(w[0][j]));
+        } else if constexpr (R == 2) {
+            g[2 * j] = mean_fp32(bf16_lo(w[0][j]), bf16_lo(w[1][j]));
+            g[2 * j + 1] = mean_fp32(bf16_hi(w[0][j]), bf16_hi(w[1][j]));
+        } else {
+            double s_lo = 0.0, s_hi = 0.0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                s_lo += (double)bf16_lo(w[r][j]);
+                s_hi += (double)bf16_hi(w[r][j]);
+                span_add(sp, w[r][j]);
+            }
+            g[2 * j] = mean_of<R>(s_lo);
+            g[2 * j + 1] = mean_of<R>(s_hi);
+        }
+    }
+}
+
+// Fast route for 2W elements; returns false if the values fail span_exact.
 template <int R, int W>
 __device__ __forceinline__ bool means_fast(const uint32_t (&w)[R][W], float (&g)[2 * W]) {
     Span sp = span_init();
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-        double s_lo = 0.0, s_hi = 0.0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            s_lo += (double)bf16_lo(w[r][j]);
-            s_hi += (double)bf16_hi(w[r][j]);
-            if constexpr (R > 1) span_add(sp, w[r][j]);
-        }
-        g[2 * j] = mean_of<R>(s_lo);
-        g[2 * j + 1] = mean_of<R>(s_hi);
-    }
-    if constexpr (R > 1) return span_exact<R>(sp);
+    means_of<R, W>(w, g, sp);
+    if constexpr (R > 2) return span_exact<R>(sp);
     return true;
 }
 
@@ -256,37 +294,38 @@ __device__ __forceinline__ bool means_fast(const uint32_t (&w)[R][W], float (&g)
 template <int R>
 __device__ __forceinline__ void mean4(const uint32_t (&w)[R][2], const uint16_t *const *g, int64_t e0,
                                       float (&out)[4]) {
-    if (__builtin_expect(!means_fast<R, 2>(w, out), 0)) {
-        const float4 t = mean_wide_at4<R>(g, e0);
-        out[0] = t.x;
-        out[1] = t.y;
-        out[2] = t.z;
-        out[3] = t.w;
+    const bool fast = means_fast<R, 2>(w, out);
+    if constexpr (R > 2) {
+        if (__builtin_expect(!fast, 0)) {
+            const float4 t = mean_wide_at4<R>(g, e0);
+            out[0] = t.x;
+            out[1] = t.y;
+            out[2] = t.z;
+            out[3] = t.w;
+        }
     }
 }
 
 // g_bar of element i of the R buffers g[r].
 template <int R>
 __device__ __forceinline__ float mean1(const uint16_t *const *g, int64_t i) {
-    uint32_t v[R];
-    double s = 0.0;
-    Span sp = span_init();
+    uint32_t w[R][1];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        v[r] = g[r][i];
-        s += (double)__uint_as_float(v[r] << 16);
-        span_add(sp, v[r]);
-    }
-    if constexpr (R > 1)
-        if (!span_exact<R>(sp)) return mean_wide_at<R>(g, i);
-    return mean_of<R>(s);
+    for (int r = 0; r < R; ++r) w[r][0] = g[r][i];
+    float m[2];
+    const bool fast = means_fast<R, 1>(w, m);
+    if constexpr (R > 2)
+        if (!fast) return mean_wide_at<R>(g, i);
+    return m[0];
 }
 
 // Double-double accumulation.  S is the sum of the squares of FP32 values,
-// each exact in FP64; it is carried as an unevaluated pair hi + lo (about
-// 106 significant bits), so its final rounding to FP64 is that of the exact
-// sum except when the exact sum lies within ~1e-28 of an FP64 rounding
-// boundary.  two_sum is Knuth's error-free addition.
+// each exact in FP64; it is carried as an unevaluated pair hi + lo, hi an FP64
+// sum and lo the sum of its rounding errors (relative error below 2^-85, most
+// of it from lo's own rounding), so its final rounding to FP64 is that of the
+// exact sum, in whatever order and spans it is summed, except when the exact
+// sum lies within that distance of an FP64 rounding boundary.  two_sum is
+// Knuth's error-free addition.
 __device__ __forceinline__ void dd_add(double &hi, double &lo, double x) {
     const double s = hi + x;
     const double bb = s - hi;
@@ -304,51 +343,84 @@ __device__ __forceinline__ void dd_merge(double &hi, double &lo, double bhi, dou
     lo = e - (hi - s);
 }
 
-__device__ __forceinline__ void wave_merge(double &hi, double &lo) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double oh = __shfl_xor(hi, off, 64);
-        const double ol = __shfl_xor(lo, off, 64);
-        dd_merge(hi, lo, oh, ol);
-    }
+// The lane's partner in step STEP of the butterfly: lane ^ 1, lane ^ 2, then
+// (the quads being uniform by then) the mirrored lane of the half row and of
+// the row, lane ^ 16 and lane ^ 32.  The first four are register moves within
+// a row of 16 lanes (DPP); a shuffle through LDS took about three times as
+// long per step.
+template <int STEP>
+__device__ __forceinline__ int partner_word(int x) {
+    if constexpr (STEP == 0) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xf, 0xf, true);        // quad_perm 1,0,3,2
+    else if constexpr (STEP == 1) return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xf, 0xf, true);   // quad_perm 2,3,0,1
+    else if constexpr (STEP == 2) return __builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, true);  // row_half_mirror
+    else if constexpr (STEP == 3) return __builtin_amdgcn_mov_dpp(x, 0x140, 0xf, 0xf, true);  // row_mirror
+    else return __shfl_xor(x, STEP == 4 ? 16 : 32, 64);
 }
 
-// Block sum of one pair per thread in a fixed order: a fixed butterfly inside
-// each wave, then the waves in index order.  Valid in thread 0.
+template <int STEP>
+__device__ __forceinline__ double partner(double x) {
+    return __hiloint2double(partner_word<STEP>(__double2hiint(x)), partner_word<STEP>(__double2loint(x)));
+}
+
+// Adds a pair to a pair without renormalising: hi stays an FP64 sum, every
+// rounding error of which goes to lo.
+__device__ __forceinline__ void dd_add_pair(double &hi, double &lo, double bhi, double blo) {
+    dd_add(hi, lo, bhi);
+    lo += blo;
+}
+
+template <int STEP>
+__device__ __forceinline__ void wave_merge_step(double &hi, double &lo) {
+    const double bh = partner<STEP>(hi), bl = partner<STEP>(lo);
+    // the same bits in both partners: every operation here is symmetric
+    // (a TwoSum's error term is exact whichever operand comes first)
+    const double s = hi + bh;
+    const double t = s - hi;
+    const double e = (hi - (s - t)) + (bh - t);
+    lo = (lo + bl) + e;
+    hi = s;
+}
+
+__device__ __forceinline__ void wave_merge(double &hi, double &lo) {
+    wave_merge_step<0>(hi, lo);
+    wave_merge_step<1>(hi, lo);
+    wave_merge_step<2>(hi, lo);
+    wave_merge_step<3>(hi, lo);
+    wave_merge_step<4>(hi, lo);
+    wave_merge_step<5>(hi, lo);
+}
+
+// Block sum of one pair per thread in a fixed order, valid in thread 0: lane
+// l of the first wave adds the pairs of threads l, l + 64, l + 128, ... in
+// that order, then a fixed butterfly.  Only one wave runs the butterfly: in
+// every wave it cost as much as the sums themselves.
 template <int THREADS>
 __device__ __forceinline__ void block_merge(double &hi, double &lo) {
-    __shared__ double ws_hi[THREADS / 64], ws_lo[THREADS / 64];
-    wave_merge(hi, lo);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) {
-        ws_hi[wave] = hi;
-        ws_lo[wave] = lo;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        hi = ws_hi[0];
-        lo = ws_lo[0];
+    if constexpr (THREADS > 64) {
+        __shared__ double2 pairs[THREADS - 64];
+        if (threadIdx.x >= 64) pairs[threadIdx.x - 64] = make_double2(hi, lo);
+        __syncthreads();
+        if (threadIdx.x >= 64) return;
 #pragma unroll
-        for (int k = 1; k < THREADS / 64; ++k) dd_merge(hi, lo, ws_hi[k], ws_lo[k]);
+        for (int k = 0; k < THREADS / 64 - 1; ++k) {
+            const double2 b = pairs[k * 64 + threadIdx.x];
+            dd_add_pair(hi, lo, b.x, b.y);
+        }
     }
+    wave_merge(hi, lo);
 }
 
 // ---------------------------------------------------------------------------
-// Norm partials: each tile is split into kNormSplit spans of kNormSpan
-// elements, and block b sums g_bar^2 over span b of the segment (the grid is
-// kNormSplit blocks per tile, those past the end write a zero pair).  Lanes
-// read 4 elements per rank at a time (8-byte loads); when g_bar is stored,
-// each lane's 4 FP32 results go out as one 16-byte store, contiguous across
-// the wave.  Lane t handles the 4-element groups b*1024 + 256*j + t in
-// increasing j; the read-only pass issues two groups before either is
-// consumed, the pass that stores g_bar one (it runs under a residency cap,
-// and more loads in flight per lane measured slower there).  Gradients and
-// g_bar move with non-temporal loads and stores: they are not reused within
-// the pass, and the 256 MB last-level cache cannot hold them until the
-// update reads g_bar back.  The ragged tail of fewer than V
-// elements is added by lane 0 of its span after the groups.  The per-lane
-// order, the butterfly and the wave order are fixed, so a span's partial
-// depends on its contents only.
+// Norm partials: a segment is split into spans of NormShape<R, STORE>::kSpan
+// elements, block b sums g_bar^2 over span b, and the blocks of a launch
+// cover whole tiles (those past the end write a zero pair).  Lane t of a
+// block handles the V-element groups b*kSpan/V + k*T + t (k increasing).
+// A lane's order, the butterfly and the wave order are fixed, so a span's
+// partial depends on its contents only.
+//
+// Gradients and g_bar move with non-temporal loads and stores: they are not
+// reused within the pass, and the 256 MB last-level cache cannot hold them
+// until the update reads g_bar back.
 __device__ __forceinline__ uint4 load_stream(const uint16_t *p) {
     const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
     return make_uint4(t.x, t.y, t.z, t.w);
@@ -365,74 +437,149 @@ __device__ __forceinline__ void load_stream_v(const uint16_t *p, uint32_t (&w)[V
     }
 }
 
-template <int R, bool WRITE_GBAR>
-__global__ __launch_bounds__(kNormThreads) void k_norm_partials(NormArgs a) {
-    constexpr int V = 4;
-    constexpr int kGroupsPerSpan = kNormSpan / V;
-    constexpr int kUnroll = WRITE_GBAR ? 1 : 2;
-    constexpr int kIters = kGroupsPerSpan / (kNormThreads * kUnroll);
-    static_assert(kIters * kNormThreads * kUnroll == kGroupsPerSpan, "span must split evenly over the lanes");
-    const int64_t n = a.n;
-    const int64_t full_groups = n / V;
-    const int64_t span0 = (int64_t)blockIdx.x * kGroupsPerSpan;
-    double hi = 0.0, lo = 0.0;
-    uint32_t wide = 0;  // bit (it * kUnroll + u): a group that takes the wide route
-    for (int it = 0; it < kIters; ++it) {
-        uint32_t raw[kUnroll][R][V / 2];
-        bool ok[kUnroll];
+// A power of two that is at least the square of every value of magnitude
+// below 2^(e - 126), where e is the biased exponent of the largest magnitude
+// among a lane's values (of the gradients, which bound their mean, or of the
+// means).
+__device__ __forceinline__ double square_anchor(uint32_t e) {
+    return __hiloint2double((int)((2u * e + 771u) << 20), 0);  // 2^(2e - 252)
+}
+
+// Sum of the squares of one lane's K means, as a pair.  Every square is
+// exact in FP64 (48 bits) and at most the anchor, so with the running sum
+// started at the anchor each addition is Dekker's Fast2Sum, whose error term
+// is exact, and the square itself need not be formed:
+// s = fma(g, g, hi), error = fma(g, g, -(s - hi)).  Four operations per value
+// where Knuth's TwoSum on the product takes eight.  The anchor leaves hi
+// exactly at the end (hi is a multiple of its last bit).  What is rounded is
+// lo alone, to 2^-53 of itself: below 2^-90 of the largest square for K <= 32.
+template <int K>
+__device__ __forceinline__ void sum_squares(const float *g, uint32_t e, double &hi, double &lo) {
+    const double anchor = square_anchor(e);
+    hi = anchor;
+    lo = 0.0;
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int64_t q = span0 + (int64_t)(it * kUnroll + u) * kNormThreads + threadIdx.x;
-            ok[u] = q < full_groups;
+    for (int i = 0; i < K; ++i) {
+        const double x = (double)g[i];
+        const double s = __builtin_fma(x, x, hi);
+        lo += __builtin_fma(x, x, hi - s);
+        hi = s;
+    }
+    hi -= anchor;
+}
+
+// Biased exponent of the largest magnitude among K FP32 values.
+template <int K>
+__device__ __forceinline__ uint32_t top_exponent(const float *g) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) m = max(m, __float_as_uint(g[i]) << 1);
+    return m >> 24;
+}
+
+// The pair of span `blk` of the n-element segment g, and its g_bar if STORE.
+// Valid in thread 0.
+template <int R, bool STORE, class S>
+__device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, int64_t blk, float *gbar, double &hi,
+                                          double &lo) {
+    constexpr int V = S::kVec, T = S::kThreads, J = S::kBatch;
+    constexpr int kIters = S::kSpan / (V * T * J);
+    static_assert(kIters * V * T * J == S::kSpan, "span must split evenly over the lanes");
+    static_assert(kIters <= 32, "one bit per batch of a lane");
+    const int64_t span0 = blk * S::kSpan;
+    // whole groups of V elements of the segment in this span
+    const int64_t left = n - span0;
+    const uint32_t groups = left >= S::kSpan ? S::kSpan / V : left > 0 ? (uint32_t)left / V : 0u;
+    hi = lo = 0.0;
+    uint32_t wide = 0;  // bit `it`: a batch that takes the wide route
+    for (int it = 0; it < kIters; ++it) {
+        uint32_t raw[J][R][V / 2];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const uint32_t q = (uint32_t)(it * J + j) * T + threadIdx.x;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                if (ok[u]) {
-                    load_stream_v<V>(a.g[r] + q * V, raw[u][r]);
+                if (q < groups) {
+                    load_stream_v<V>(g[r] + span0 + q * V, raw[j][r]);
                 } else {
 #pragma unroll
-                    for (int w = 0; w < V / 2; ++w) raw[u][r][w] = 0;
+                    for (int w = 0; w < V / 2; ++w) raw[j][r][w] = 0;
                 }
             }
         }
+        float m[J * V];
+        Span sp = span_init();
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            if (!ok[u]) continue;
-            float g[V];
-            if (__builtin_expect(!means_fast<R, V / 2>(raw[u], g), 0)) {
-                wide |= 1u << (it * kUnroll + u);
-                continue;
+        for (int j = 0; j < J; ++j) means_of<R, V / 2>(raw[j], m + j * V, sp);
+        uint32_t e;
+        bool fast = true;
+        if constexpr (R > 2) {
+            fast = span_exact<R>(sp);
+            e = (uint32_t)(sp.top.x > sp.top.y ? sp.top.x : sp.top.y) >> 7;
+        } else {
+            e = top_exponent<J * V>(m);
+        }
+        double bh, bl;
+        sum_squares<J * V>(m, e, bh, bl);
+        if (__builtin_expect(fast, 1)) {
+            if constexpr (kIters == 1) {
+                hi = bh;
+                lo = bl;
+            } else {
+                dd_add_pair(hi, lo, bh, bl);
             }
+            if constexpr (STORE) {
 #pragma unroll
-            for (int e = 0; e < V; ++e) dd_add(hi, lo, (double)g[e] * (double)g[e]);
-            if constexpr (WRITE_GBAR) {
-                const int64_t e0 = (span0 + (int64_t)(it * kUnroll + u) * kNormThreads + threadIdx.x) * V;
-                store_nt4(a.gbar_out + e0, make_float4(g[0], g[1], g[2], g[3]));
+                for (int j = 0; j < J; ++j) {
+                    const uint32_t q = (uint32_t)(it * J + j) * T + threadIdx.x;
+                    if (q < groups) {
+#pragma unroll
+                        for (int h = 0; h < V / 4; ++h)
+                            store_nt4(gbar + span0 + q * V + 4 * h,
+                                      make_float4(m[j * V + 4 * h], m[j * V + 4 * h + 1], m[j * V + 4 * h + 2],
+                                                  m[j * V + 4 * h + 3]));
+                    }
+                }
+            }
+        } else {
+            wide |= 1u << it;
+        }
+    }
+    if constexpr (R > 2) {
+        // the batches that failed the span check, in the same order, after the
+        // loop, where the wide route's registers do not add to the loop's
+        while (__builtin_expect(wide != 0, 0)) {
+            const int it = __builtin_ctz(wide);
+            wide &= wide - 1;
+#pragma unroll 1
+            for (int j = 0; j < J * V / 4; ++j) {
+                const uint32_t q = (uint32_t)(it * J + j / (V / 4)) * T + threadIdx.x;
+                if (q >= groups) continue;
+                const int64_t e0 = span0 + q * V + 4 * (j % (V / 4));
+                const float4 t = mean_wide_at4<R>(g, e0);
+                dd_add(hi, lo, (double)t.x * (double)t.x);
+                dd_add(hi, lo, (double)t.y * (double)t.y);
+                dd_add(hi, lo, (double)t.z * (double)t.z);
+                dd_add(hi, lo, (double)t.w * (double)t.w);
+                if constexpr (STORE) store_nt4(gbar + e0, t);
             }
         }
     }
-    // the groups that failed the span check, in the same order, after the
-    // loop, where the wide route's registers do not add to the loop's
-    static_assert(kIters * kUnroll <= 32, "one bit per group of a lane");
-    while (__builtin_expect(wide != 0, 0)) {
-        const int k = __builtin_ctz(wide);
-        wide &= wide - 1;
-        const int64_t e0 = (span0 + (int64_t)k * kNormThreads + threadIdx.x) * V;
-        const float4 t = mean_wide_at4<R>(a.g, e0);
-        dd_add(hi, lo, (double)t.x * (double)t.x);
-        dd_add(hi, lo, (double)t.y * (double)t.y);
-        dd_add(hi, lo, (double)t.z * (double)t.z);
-        dd_add(hi, lo, (double)t.w * (double)t.w);
-        if constexpr (WRITE_GBAR) store_nt4(a.gbar_out + e0, t);
-    }
-    const int64_t tail0 = full_groups * V;
-    if (threadIdx.x == 0 && tail0 < n && tail0 / kNormSpan == (int64_t)blockIdx.x) {
-        for (int64_t i = tail0; i < n; ++i) {
-            float g = mean1<R>(a.g, i);
-            dd_add(hi, lo, (double)g * (double)g);
-            if constexpr (WRITE_GBAR) a.gbar_out[i] = g;
+    // the segment's ragged tail of fewer than V elements, by one lane of its span
+    if (threadIdx.x == 0 && left > 0 && left < S::kSpan) {
+        for (int64_t i = span0 + (int64_t)groups * V; i < n; ++i) {
+            const float t = mean1<R>(g, i);
+            dd_add(hi, lo, (double)t * (double)t);
+            if constexpr (STORE) gbar[i] = t;
         }
     }
-    block_merge<kNormThreads>(hi, lo);
+    block_merge<T>(hi, lo);
+}
+
+template <int R, bool WRITE_GBAR>
+__global__ __launch_bounds__((NormShape<R, WRITE_GBAR>::kThreads)) void k_norm_partials(NormArgs a) {
+    double hi, lo;
+    norm_span<R, WRITE_GBAR, NormShape<R, WRITE_GBAR>>(a.g, a.n, blockIdx.x, a.gbar_out, hi, lo);
     if (threadIdx.x == 0) {
         a.partials[2 * blockIdx.x] = hi;
         a.partials[2 * blockIdx.x + 1] = lo;
@@ -493,7 +640,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_norm_finalize(
     for (int c = 1; c < kChains; ++c) dd_merge(hi, lo, chi[c], clo[c]);
     block_merge<kFinalizeThreads>(hi, lo);
     if (threadIdx.x == 0) {
-        const double S = hi;
+        const double S = hi + lo;
         const double norm = sqrt(S);
         const int bad = !isfinite(S);
         double c = 1.0;
@@ -672,29 +819,28 @@ __global__ __launch_bounds__(kUpdateThreads) void k_update_pattern(UpdateArgs a)
 // ragged tail of fewer than 4 elements is left out.
 
 template <int R>
-__global__ __launch_bounds__(kNormThreads) void k_norm_pattern(NormArgs a) {
-    constexpr int V = 4;
-    constexpr int kGroupsPerSpan = kNormSpan / V;
-    constexpr int kIters = kGroupsPerSpan / kNormThreads;
-    const int64_t full_groups = a.n / V;
-    const int64_t span0 = (int64_t)blockIdx.x * kGroupsPerSpan;
+__global__ __launch_bounds__((NormShape<R, true>::kThreads)) void k_norm_pattern(NormArgs a) {
+    using S = NormShape<R, true>;
+    constexpr int V = S::kVec, T = S::kThreads;
+    static_assert(V == 4, "one 16-byte store per group");
+    const int64_t span0 = (int64_t)blockIdx.x * S::kSpan;
+    const int64_t left = a.n - span0;
+    const uint32_t groups = left >= S::kSpan ? S::kSpan / V : left > 0 ? (uint32_t)left / V : 0u;
     uint32_t acc = 0;
-    for (int it = 0; it < kIters; ++it) {
-        const int64_t q = span0 + (int64_t)it * kNormThreads + threadIdx.x;
-        if (q >= full_groups) break;
+    for (uint32_t q = threadIdx.x; q < groups; q += T) {
         uint32_t x0 = 0, x1 = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             uint32_t w[2];
-            load_stream_v<V>(a.g[r] + q * V, w);
+            load_stream_v<V>(a.g[r] + span0 + q * V, w);
             x0 ^= w[0];
             x1 ^= w[1];
         }
-        store_nt4(a.gbar_out + q * V, make_float4(bf16_lo(x0), bf16_hi(x0), bf16_lo(x1), bf16_hi(x1)));
+        store_nt4(a.gbar_out + span0 + q * V, make_float4(bf16_lo(x0), bf16_hi(x0), bf16_lo(x1), bf16_hi(x1)));
         acc ^= x0 ^ x1;
     }
     double hi = (double)acc, lo = 0.0;
-    block_merge<kNormThreads>(hi, lo);
+    block_merge<T>(hi, lo);
     if (threadIdx.x == 0) {
         a.partials[2 * blockIdx.x] = hi;
         a.partials[2 * blockIdx.x + 1] = lo;
@@ -790,15 +936,18 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t *__restrict__ dst, in
 // ceil(a / b) for a >= 0, b > 0, without overflow near the int64 limit
 inline int64_t cdiv(int64_t a, int64_t b) { return a / b + (a % b != 0); }
 
+template <int R, bool STORE>
+hipError_t norm_rs(const NormArgs &a, int lds_pad, hipStream_t s) {
+    using S = NormShape<R, STORE>;
+    static_assert(kTile / S::kSpan == norm_pairs_per_tile(R, STORE), "the host's pair count");
+    hipLaunchKernelGGL((k_norm_partials<R, STORE>), dim3((uint32_t)(cdiv(a.n, kTile) * (kTile / S::kSpan))),
+                       dim3(S::kThreads), lds_pad, s, a);
+    return hipGetLastError();
+}
+
 template <int R>
 hipError_t norm_r(const NormArgs &a, int store_lds_pad, hipStream_t s) {
-    const int64_t blocks = cdiv(a.n, kTile) * kNormSplit;
-    if (a.gbar_out)
-        hipLaunchKernelGGL((k_norm_partials<R, true>), dim3((uint32_t)blocks), dim3(kNormThreads), store_lds_pad, s,
-                           a);
-    else
-        hipLaunchKernelGGL((k_norm_partials<R, false>), dim3((uint32_t)blocks), dim3(kNormThreads), 0, s, a);
-    return hipGetLastError();
+    return a.gbar_out ? norm_rs<R, true>(a, store_lds_pad, s) : norm_rs<R, false>(a, 0, s);
 }
 
 template <int R>
@@ -821,8 +970,8 @@ hipError_t pattern_r(const UpdateArgs &a, int64_t blocks, int lds_pad, hipStream
 
 template <int R>
 hipError_t norm_pattern_r(const NormArgs &a, int store_lds_pad, hipStream_t s) {
-    const int64_t blocks = cdiv(a.n, kTile) * kNormSplit;
-    hipLaunchKernelGGL((k_norm_pattern<R>), dim3((uint32_t)blocks), dim3(kNormThreads), store_lds_pad, s, a);
+    const int64_t blocks = cdiv(a.n, kTile) * norm_pairs_per_tile(R, true);
+    hipLaunchKernelGGL((k_norm_pattern<R>), dim3((uint32_t)blocks), dim3(NormShape<R, true>::kThreads), store_lds_pad, s, a);
     return hipGetLastError();
 }
 

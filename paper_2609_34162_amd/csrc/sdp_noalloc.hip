@@ -43,7 +43,7 @@ using sdprt::fail;
     } while (0)
 
 constexpr int64_t kMaxTiles = SDP_NOALLOC_MAX_TILES;
-constexpr int64_t kMaxPairs = kMaxTiles * sdp::kNormSplit;
+constexpr int64_t kMaxPairs = kMaxTiles * sdp::norm_pairs_per_tile(SDP_MAX_RANKS, false);
 constexpr int64_t kMaxMerged = (kMaxPairs + sdp::kMergeRun - 1) / sdp::kMergeRun;
 constexpr size_t kPairBytes = 2 * sizeof(double);
 constexpr size_t kNormStateOffset = (size_t)(kMaxPairs + kMaxMerged) * kPairBytes;
@@ -211,17 +211,18 @@ int sdp_agg_adam_step_noalloc(const sdp_segment *segs, int32_t n_segs, const sdp
         }                                                                                              \
     } while (0)
     // norm pass over every tile of every segment, in segment then tile order
+    const int64_t ppt = sdp::norm_pairs_per_tile(R, false);  // at most kMaxPairs / kMaxTiles
     int64_t tile_base = 0;
     for (int32_t s = 0; s < n_segs; ++s) {
         sdp::NormArgs a{};
         for (int32_t r = 0; r < R; ++r) a.g[r] = segs[s].grads[r];
         a.n = segs[s].numel;
-        a.partials = partials + 2 * sdp::kNormSplit * tile_base;
+        a.partials = partials + 2 * ppt * tile_base;
         a.gbar_out = nullptr;
         NA_HIP(sdp::launch_norm_partials(R, a, 0, st));
         tile_base += (segs[s].numel / SDP_NORM_TILE + (segs[s].numel % SDP_NORM_TILE != 0));
     }
-    NA_HIP(sdp::launch_norm_finalize(partials, tiles * sdp::kNormSplit, merged, hp->max_grad_norm, ns, st));
+    NA_HIP(sdp::launch_norm_finalize(partials, tiles * ppt, merged, hp->max_grad_norm, ns, st));
     // the fused update, reading the clip coefficient from the norm state,
     // with the per-step constants computed as for every other mode
     for (int32_t s = 0; s < n_segs; ++s) {

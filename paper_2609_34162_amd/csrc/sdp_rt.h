@@ -262,7 +262,8 @@ struct sdp_ctx {
     sdp::NormState *ns_host = nullptr;  // pinned mirror for read-back
     int update_max_blocks = 0;     // 0: one 8-element group per lane
     int update_lds_pad = 0;        // dynamic LDS bytes per update block (residency cap); 0: no cap
-    int norm_store_lds_pad = 0;    // the same for the norm pass that stores g_bar
+    int norm_store_blocks = -1;    // SDP_NORM_STORE_BLOCKS_PER_CU, or -1: norm_store_blocks_per_cu(R)
+    int lds_cu = 0, lds_block = 0;  // LDS bytes of a compute unit, and the most that a block may have
     bool timing = false;
     std::vector<sdprt::Timed> timed;
     // host lanes of the host-update route, timed on the host clock
@@ -294,8 +295,8 @@ int check_chunk(int64_t chunk, bool allow_zero);
 
 // ---- workspace ----------------------------------------------------------
 
-int ensure_partials(sdp_ctx *ctx, int64_t tiles);
-double *tile_partials(sdp_ctx *ctx, int64_t tile);  // the first pair of a tile's span partials
+int ensure_partials(sdp_ctx *ctx, int64_t pairs);
+double *tile_partials(sdp_ctx *ctx, int64_t tile, int pairs_per_tile);  // the first pair of a tile's span partials
 int ensure_gbar(sdp_ctx *ctx, int64_t n);
 // Layout of one call: norm tiles and stored-g_bar offsets of each segment.
 struct Plan {
@@ -313,9 +314,11 @@ void timed_end(sdp_ctx *ctx, hipStream_t s, hipEvent_t a, int kind, int64_t elem
 
 // ---- launches and ordering shared by the modes ---------------------------
 
+int residency_pad(const sdp_ctx *ctx, int per_cu, int static_lds);
+int norm_store_lds_pad(const sdp_ctx *ctx, int32_t R);
 int norm_launch(sdp_ctx *ctx, int32_t R, const uint16_t *const *g, int64_t n, double *partials, float *gbar_out,
                 hipStream_t s);
-int finalize_launch(sdp_ctx *ctx, int64_t tiles, double max_grad_norm, hipStream_t s);
+int finalize_launch(sdp_ctx *ctx, int64_t pairs, double max_grad_norm, hipStream_t s);
 void fill_consts(const sdp_adamw_params *hp, sdp::UpdateArgs &a);
 int update_launch(sdp_ctx *ctx, int32_t R, const sdp_adamw_params *hp, float *p, float *m, float *v, uint16_t *pb,
                   const uint16_t *const *g, const float *gbar, int64_t n, hipStream_t s);

@@ -192,25 +192,25 @@ int check_chunk(int64_t chunk, bool allow_zero) {
 
 // ---- workspace ----------------------------------------------------------
 
-double *tile_partials(sdp_ctx *ctx, int64_t tile) { return ctx->partials + 2 * sdp::kNormSplit * tile; }
+double *tile_partials(sdp_ctx *ctx, int64_t tile, int pairs_per_tile) {
+    return ctx->partials + 2 * pairs_per_tile * tile;
+}
 
-int ensure_partials(sdp_ctx *ctx, int64_t tiles) {
-    const int64_t n = tiles * sdp::kNormSplit;
-    if (n <= ctx->partials_cap) return SDP_OK;
+int ensure_partials(sdp_ctx *ctx, int64_t pairs) {
+    if (pairs <= ctx->partials_cap) return SDP_OK;
     HIP_TRY(hipDeviceSynchronize());
     if (ctx->partials) HIP_TRY(hipFree(ctx->partials));
     ctx->partials = nullptr;
     ctx->partials_cap = 0;
-    int64_t cap = std::max<int64_t>(n, 4096);
     // each span partial is a double-double pair; the finalize's first stage
     // writes one pair per kMergeRun of them after the last
-    const int64_t pairs = cap + cdiv(cap, sdp::kMergeRun);
-    if (hipMalloc(&ctx->partials, (size_t)pairs * 2 * sizeof(double)) != hipSuccess) {
+    const int64_t room = pairs + cdiv(pairs, sdp::kMergeRun);
+    if (hipMalloc(&ctx->partials, (size_t)room * 2 * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
         ctx->partials = nullptr;
-        return fail(SDP_ERR_OUT_OF_MEMORY, "cannot allocate %lld norm partials", (long long)cap);
+        return fail(SDP_ERR_OUT_OF_MEMORY, "cannot allocate %lld norm partials", (long long)pairs);
     }
-    ctx->partials_cap = cap;
+    ctx->partials_cap = pairs;
     return SDP_OK;
 }
 
@@ -291,6 +291,19 @@ void timed_end(sdp_ctx *ctx, hipStream_t s, hipEvent_t a, int kind, int64_t elem
 
 // ---- launches shared by the modes ------------------------------------------
 
+// Dynamic LDS bytes per block that keep at most per_cu blocks (of static_lds
+// bytes of their own) on a compute unit; 0: no cap.
+int residency_pad(const sdp_ctx *ctx, int per_cu, int static_lds) {
+    if (per_cu <= 0) return 0;
+    const int pad = (ctx->lds_cu / per_cu - static_lds) / 1024 * 1024;
+    return pad > 0 && pad + static_lds <= ctx->lds_block ? pad : 0;
+}
+
+int norm_store_lds_pad(const sdp_ctx *ctx, int32_t R) {
+    const int per_cu = ctx->norm_store_blocks >= 0 ? ctx->norm_store_blocks : sdp::norm_store_blocks_per_cu(R);
+    return residency_pad(ctx, per_cu, sdp::norm_static_lds(R, true));
+}
+
 int norm_launch(sdp_ctx *ctx, int32_t R, const uint16_t *const *g, int64_t n, double *partials, float *gbar_out,
                 hipStream_t s) {
     sdp::NormArgs a{};
@@ -299,16 +312,16 @@ int norm_launch(sdp_ctx *ctx, int32_t R, const uint16_t *const *g, int64_t n, do
     a.partials = partials;
     a.gbar_out = gbar_out;
     hipEvent_t t0 = timed_begin(ctx, s);
-    HIP_TRY(sdp::launch_norm_partials(R, a, ctx->norm_store_lds_pad, s));
+    HIP_TRY(sdp::launch_norm_partials(R, a, norm_store_lds_pad(ctx, R), s));
     timed_end(ctx, s, t0, kNorm, n);
     return SDP_OK;
 }
 
-int finalize_launch(sdp_ctx *ctx, int64_t tiles, double max_grad_norm, hipStream_t s) {
+int finalize_launch(sdp_ctx *ctx, int64_t pairs, double max_grad_norm, hipStream_t s) {
     hipEvent_t t0 = timed_begin(ctx, s);
-    HIP_TRY(sdp::launch_norm_finalize(ctx->partials, tiles * sdp::kNormSplit, ctx->partials + 2 * ctx->partials_cap,
-                                      max_grad_norm, ctx->ns, s));
-    timed_end(ctx, s, t0, kFinalize, tiles);
+    HIP_TRY(sdp::launch_norm_finalize(ctx->partials, pairs, ctx->partials + 2 * ctx->partials_cap, max_grad_norm,
+                                      ctx->ns, s));
+    timed_end(ctx, s, t0, kFinalize, pairs);
     return SDP_OK;
 }
 
@@ -400,10 +413,11 @@ int sync_streams(sdp_ctx *ctx) {
 
 int device_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool store_gbar,
                 double max_grad_norm, hipStream_t s) {
+    const int ppt = sdp::norm_pairs_per_tile(R, store_gbar);
     for (int32_t k = 0; k < n_segs; ++k)
-        SDP_TRY(norm_launch(ctx, R, segs[k].grads, segs[k].numel, tile_partials(ctx, plan.tile_base[k]),
+        SDP_TRY(norm_launch(ctx, R, segs[k].grads, segs[k].numel, tile_partials(ctx, plan.tile_base[k], ppt),
                             store_gbar ? ctx->gbar + plan.gbar_base[k] : nullptr, s));
-    return finalize_launch(ctx, plan.tiles, max_grad_norm, s);
+    return finalize_launch(ctx, plan.tiles * ppt, max_grad_norm, s);
 }
 
 // ---- chunks and staging slots -------------------------------------------
@@ -721,15 +735,14 @@ int sdp_ctx_create(sdp_ctx **out, int device, int64_t max_chunk_elems, int32_t m
             (void)hipGetLastError();
             return bail(fail(SDP_ERR_HIP, "cannot query the device's LDS size"));
         }
-        auto pad_for = [&](const char *env_name, int per_cu, int static_lds) {
-            if (const char *env = std::getenv(env_name)) per_cu = std::max(0, std::atoi(env));
-            if (per_cu <= 0) return 0;
-            const int pad = (lds_cu / per_cu - static_lds) / 1024 * 1024;
-            return pad > 0 && pad + static_lds <= lds_block ? pad : 0;
+        auto from_env = [](const char *name, int otherwise) {
+            const char *env = std::getenv(name);
+            return env ? std::max(0, std::atoi(env)) : otherwise;
         };
-        c->update_lds_pad = pad_for("SDP_UPDATE_BLOCKS_PER_CU", sdp::kUpdateBlocksPerCU, 0);
-        // the norm pass's own LDS: two 4-entry FP64 arrays for the block merge
-        c->norm_store_lds_pad = pad_for("SDP_NORM_STORE_BLOCKS_PER_CU", sdp::kNormStoreBlocksPerCU, 64);
+        c->lds_cu = lds_cu;
+        c->lds_block = lds_block;
+        c->update_lds_pad = residency_pad(c, from_env("SDP_UPDATE_BLOCKS_PER_CU", sdp::kUpdateBlocksPerCU), 0);
+        c->norm_store_blocks = from_env("SDP_NORM_STORE_BLOCKS_PER_CU", -1);
     }
 #define CTX_HIP(expr)                                                                                \
     do {                                                                                             \
@@ -799,7 +812,7 @@ int sdp_ctx_create(sdp_ctx **out, int device, int64_t max_chunk_elems, int32_t m
         c->copier = new_pool(c, default_host_threads());
         c->staged_copy_threads = default_staged_copy_threads();
     }
-    rc = ensure_partials(c, 4096);
+    rc = ensure_partials(c, 65536);
     if (rc != SDP_OK) return bail(rc);
 #undef CTX_HIP
     *out = c;
@@ -851,7 +864,7 @@ int sdp_agg_adam_step(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, con
     SDP_TRY(validate_segments(ctx, segs, n_segs, kDeviceMem, kDeviceMem, false, &R));
     const Plan plan = make_plan(segs, n_segs);
     const bool store = device_gbar(ctx, R);
-    SDP_TRY(ensure_partials(ctx, plan.tiles));
+    SDP_TRY(ensure_partials(ctx, plan.tiles * sdp::norm_pairs_per_tile(R, store)));
     if (store) SDP_TRY(ensure_gbar(ctx, plan.gbar_elems));
     hipStream_t s = (hipStream_t)stream;
     SDP_TRY(order_after_last(ctx, s));
@@ -881,7 +894,7 @@ int sdp_grad_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int dev
     if (device_resident) {
         SDP_TRY(validate_segments(ctx, segs, n_segs, kDeviceMem, kDeviceMem, true, &R));
         const Plan p = make_plan(segs, n_segs);
-        SDP_TRY(ensure_partials(ctx, p.tiles));
+        SDP_TRY(ensure_partials(ctx, p.tiles * sdp::norm_pairs_per_tile(R, false)));
         hipStream_t s = (hipStream_t)stream;
         SDP_TRY(order_after_last(ctx, s));
         SDP_TRY(device_norm(ctx, segs, n_segs, R, p, false, 0.0, s));
@@ -890,7 +903,7 @@ int sdp_grad_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int dev
     } else {
         SDP_TRY(stream_common_checks(ctx, segs, n_segs, chunk_elems, true, &R));
         const Plan p = make_plan(segs, n_segs);
-        SDP_TRY(ensure_partials(ctx, p.tiles));
+        SDP_TRY(ensure_partials(ctx, p.tiles * sdp::norm_pairs_per_tile(R, false)));
         const std::vector<Chunk> chunks =
             make_chunks(segs, n_segs, sdp_sched::norm_phase_chunk(chunk_elems, R, staged(ctx)));
         SDP_TRY(order_after_last(ctx, ctx->s_copy));
@@ -1049,8 +1062,7 @@ int sdp_probe_norm_pattern(sdp_ctx *ctx, const sdp_segment *seg, void *stream) {
     DeviceGuard guard(ctx->device);
     int32_t R = 0;
     SDP_TRY(validate_segments(ctx, seg, 1, kDeviceMem, kDeviceMem, false, &R));
-    const int64_t tiles = cdiv(seg->numel, SDP_NORM_TILE);
-    SDP_TRY(ensure_partials(ctx, tiles));
+    SDP_TRY(ensure_partials(ctx, cdiv(seg->numel, SDP_NORM_TILE) * sdp::norm_pairs_per_tile(R, true)));
     SDP_TRY(ensure_gbar(ctx, seg->numel));
     hipStream_t s = (hipStream_t)stream;
     SDP_TRY(order_after_last(ctx, s));
@@ -1059,7 +1071,7 @@ int sdp_probe_norm_pattern(sdp_ctx *ctx, const sdp_segment *seg, void *stream) {
     a.n = seg->numel;
     a.partials = ctx->partials;
     a.gbar_out = ctx->gbar;
-    HIP_TRY(sdp::launch_norm_pattern(R, a, ctx->norm_store_lds_pad, s));
+    HIP_TRY(sdp::launch_norm_pattern(R, a, norm_store_lds_pad(ctx, R), s));
     SDP_TRY(mark_done(ctx, s));
     return SDP_OK;
 }

@@ -158,6 +158,7 @@ int drain(sdp_ctx *ctx, int bo, int width) {
 int stream_norm_phase(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan,
                       const std::vector<Chunk> &chunks, bool store_gbar, double max_grad_norm, bool used[2]) {
     (void)n_segs;
+    const int ppt = sdp::norm_pairs_per_tile(R, store_gbar);
     for (size_t k = 0; k < chunks.size(); ++k) {
         const Chunk &c = chunks[k];
         const int sl = (int)(k & 1);
@@ -176,13 +177,13 @@ int stream_norm_phase(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int
         HIP_TRY(hipEventRecord(ctx->h2d_done[sl], ctx->s_copy));
         HIP_TRY(hipStreamWaitEvent(ctx->s_comp, ctx->h2d_done[sl], 0));
         SDP_TRY(jitter_stream(ctx, ctx->s_comp));
-        SDP_TRY(norm_launch(ctx, R, gp, c.len, tile_partials(ctx, plan.tile_base[c.seg] + c.off / SDP_NORM_TILE),
+        SDP_TRY(norm_launch(ctx, R, gp, c.len, tile_partials(ctx, plan.tile_base[c.seg] + c.off / SDP_NORM_TILE, ppt),
                             store_gbar ? ctx->gbar + plan.gbar_base[c.seg] + c.off : nullptr, ctx->s_comp));
         SDP_TRY(poison(ctx, sl));
         HIP_TRY(hipEventRecord(ctx->slot_free[sl], ctx->s_comp));
         used[sl] = true;
     }
-    return finalize_launch(ctx, plan.tiles, max_grad_norm, ctx->s_comp);
+    return finalize_launch(ctx, plan.tiles * ppt, max_grad_norm, ctx->s_comp);
 }
 
 namespace {
@@ -271,7 +272,7 @@ int sdp_stream_step(sdp_ctx *ctx, const sdp_segment *host_segs, int32_t n_segs, 
     SDP_TRY(stream_common_checks(ctx, host_segs, n_segs, chunk_elems, false, &R));
     const Plan plan = make_plan(host_segs, n_segs);
     const bool store = !(ctx->flags & SDP_FLAG_STREAM_GBAR_NEVER);
-    SDP_TRY(ensure_partials(ctx, plan.tiles));
+    SDP_TRY(ensure_partials(ctx, plan.tiles * sdp::norm_pairs_per_tile(R, store)));
     if (store) SDP_TRY(ensure_gbar(ctx, plan.gbar_elems));
     const std::vector<Chunk> chunks = make_chunks(host_segs, n_segs, chunk_elems);
     const std::vector<Chunk> norm_chunks =

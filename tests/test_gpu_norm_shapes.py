@@ -1,0 +1,51 @@
+"""GPU: the norm pass at the edges of its spans and lane groups.  The sum of
+squares is carried as a pair of FP64 numbers to at least 2^-85 of itself, so
+its FP64 rounding, and with it the norm, is the oracle's, which rounds the
+exact sum once; the comparison is therefore of bits."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_util import DevState, check_state, hp_pair, log, need_gpu, rand_inputs, torch
+
+pytestmark = pytest.mark.gpu
+
+# one-wave spans of 256, block spans of 4,096 and 8,192, groups of 4 and 8, tiles of 65,536
+SIZES = [3, 255, 256, 257, 263, 4095, 4096, 4100, 8185, 8191, 8192, 8193, 65535, 65536 + 8193]
+
+
+@pytest.fixture(scope="module")
+def sdp():
+    return need_gpu()
+
+
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 5, 6, 7, 8, 12, 16])
+@pytest.mark.parametrize("store", [False, True])
+def test_norm_bits_at_span_edges(sdp, R, store):
+    log(f"norm shapes R={R} store={store}")
+    ctx = sdp.sdp_ctx_create(0, 0, R, sdp.SDP_FLAG_DEVICE_GBAR_ALWAYS if store else sdp.SDP_FLAG_DEVICE_GBAR_NEVER)
+    rng = np.random.default_rng(100 * R + store)
+    try:
+        for n in SIZES:
+            masters, grads = rand_inputs([n], R, 1, seed=31 * n + R)
+            for kind in ("normal", "wide", "zeros"):
+                gs = [g.copy() for g in grads[0][0]]
+                for g in gs:
+                    if kind == "wide":  # binades from 2^-60 to 2^60, some lanes beyond the fast route's window
+                        e = rng.integers(67, 188, n).astype(np.uint16) << 7
+                        g[:] = e | (g & 0x807f)
+                    elif kind == "zeros":
+                        g[rng.random(n) < 0.5] = rng.choice([0, 0x8000])
+                dev = DevState(masters, R)
+                dev.set_grads([gs])
+                hs, ho = hp_pair(sdp, lr=1e-3, weight_decay=0.02, max_grad_norm=0.05, step=3)
+                ref = oracle.State(masters)
+                _, onorm = oracle.step(ref, [gs], ho)
+                s = torch.cuda.current_stream()
+                norm = sdp.sdp_agg_adam_step(ctx, dev.segments(sdp), hs, 0, s, want_norm=True)
+                assert norm == onorm, (n, kind, norm, onorm)
+                assert sdp.sdp_grad_norm(ctx, dev.segments(sdp), True, 0, s) == onorm, (n, kind)
+                check_state(dev.host(), ref)
+    finally:
+        sdp.sdp_ctx_destroy(ctx)

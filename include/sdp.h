@@ -188,9 +188,10 @@ typedef struct {
  * max_ranks in 1..SDP_MAX_RANKS bounds R for streamed mode staging.  The
  * context creates two streams (default priority) and its events.  Other
  * workspace (norm partials, cached g_bar) grows on demand.  The fused update
- * keeps at most 10 of its one-wave blocks on a compute unit, and the norm
- * pass that stores g_bar at most 4 of its blocks, through dynamic LDS that
- * they do not use; the environment variables SDP_UPDATE_BLOCKS_PER_CU and
+ * keeps at most 11 of its one-wave blocks on a compute unit (12 in a launch
+ * over several segments), and the norm pass that stores g_bar at most 4 of its
+ * 256-thread blocks (R <= 4) or 14 to 24 of its one-wave blocks (R > 4),
+ * through dynamic LDS that they do not use; the environment variables SDP_UPDATE_BLOCKS_PER_CU and
  * SDP_NORM_STORE_BLOCKS_PER_CU, read here, set other caps (0: none). */
 SDP_API int sdp_ctx_create(sdp_ctx **out, int device, int64_t max_chunk_elems,
                    int32_t max_ranks, uint32_t flags);
@@ -210,8 +211,8 @@ SDP_API void sdp_ctx_destroy(sdp_ctx *ctx);
  * fused update over every element; the update reads the clip coefficient and
  * the non-finite flag from device memory, so nothing returns to the host.
  * chunk_elems (0 or a multiple of SDP_NORM_TILE) names the unit the caller
- * works in; results never depend on it, and each segment is covered by one
- * launch per kernel.  Asynchronous unless grad_norm_out is non-NULL: then the
+ * works in; results never depend on it, and one launch per kernel covers up to
+ * 19 to 32 segments (by the number of ranks).  Asynchronous unless grad_norm_out is non-NULL: then the
  * call waits for the stream, stores the pre-clip norm, and returns
  * SDP_ERR_NONFINITE if it is not finite (states unchanged).  Without
  * grad_norm_out a non-finite norm still leaves the states unchanged, and

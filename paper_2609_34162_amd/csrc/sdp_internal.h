@@ -32,16 +32,10 @@ struct NormArgs {
     float *gbar_out;
 };
 
-// One launch of the fused update over `n` elements.  Gradients come either
-// from the R BF16 buffers or, when gbar is non-null, from stored g_bar.
-struct UpdateArgs {
-    float *p, *m, *v;
-    uint16_t *pb;
-    const uint16_t *g[SDP_MAX_RANKS];
-    const float *gbar;
-    int64_t n;
+// What an update needs beside its segment: the norm state and the per-step
+// constants, computed once on the host in FP64.
+struct UpdateConsts {
     const NormState *ns;
-    // per-step constants, computed once on the host in FP64
     double lr_wd;      // lr * weight_decay
     double beta1, one_minus_beta1;
     double beta2, one_minus_beta2;
@@ -49,6 +43,34 @@ struct UpdateArgs {
     double inv_bc2;    // 1 / (1 - beta2^t)
     double eps;
 };
+
+// One launch of the fused update over `n` elements.  Gradients come either
+// from the R BF16 buffers or, when gbar is non-null, from stored g_bar.
+struct UpdateArgs : UpdateConsts {
+    float *p, *m, *v;
+    uint16_t *pb;
+    const uint16_t *g[SDP_MAX_RANKS];
+    const float *gbar;
+    int64_t n;
+    int64_t stride;  // groups between a lane's passes (set by the launch)
+};
+
+// One segment of a call on several: its states, its R rank gradients (or
+// stored g_bar, which the norm pass writes and the update reads; NULL: none)
+// and its size.  The norm pass reads g, gbar and n only.
+struct Segment {
+    float *p, *m, *v;
+    uint16_t *pb;
+    const uint16_t *const *g;
+    float *gbar;
+    int64_t n;
+};
+// Segments that one launch covers: their pointers travel as kernel arguments,
+// which are kept within 4 KiB.
+constexpr int kMaxSegsPerLaunch = 32;
+constexpr int segs_per_launch(int R) {
+    return 3712 / (8 * (R + 8)) < kMaxSegsPerLaunch ? 3712 / (8 * (R + 8)) : kMaxSegsPerLaunch;
+}
 
 // One launch of the mean-gradient kernel of the host-update route: g_bar of
 // `n` elements from the R BF16 buffers, written to `out` as FP32 or, when
@@ -114,8 +136,13 @@ constexpr int kUpdateThreads = 64;
 // seven read and four write streams runs faster with fewer waves in flight
 // than the registers would allow; the cap is imposed with dynamic LDS that
 // the kernel does not use (the LDS of a compute unit divided by the cap, per
-// block).
-constexpr int kUpdateBlocksPerCU = 10;
+// block).  Measured, us per step at a cap of 8 / 10 / 11 / 12 / 14:
+// Qwen3-8B layer 1275 / 1253 / 1248 / 1249 / 1258, Qwen2.5-72B layer 6955 /
+// 6780 / 6723 / 6751 / 6857.  The kernel for several segments looks its
+// segment up first and so takes one wave more: 26 segments, R = 1, 3122 / 2952
+// / 2863 / 2832 / 2873; nine, R = 4, 361 / 356 / 356 / 359 / 363.
+constexpr int kUpdateBlocksPerCU = 11;
+constexpr int kUpdateSegmentsBlocksPerCU = 12;
 // The norm pass that stores g_bar is capped the same way.  One-wave blocks
 // (more than four ranks): the fewer ranks, the more waves it takes to keep the
 // same bytes in flight.  Best caps measured: 24 at R = 5, 20 at 6 and 7, 15-16
@@ -130,10 +157,19 @@ constexpr int kVec = 8;     // elements per lane per access (16 B of BF16, 32 B 
 constexpr int kUpdVec = 4;  // fused update: elements per lane (8 B of BF16, 16 B of FP32)
 
 hipError_t launch_norm_partials(int R, const NormArgs &a, int store_lds_pad, hipStream_t s);
+// The norm pass over n segments (all with gbar or none), in as few launches
+// as their arguments allow.  partials: the first pair of the first segment;
+// each segment's pairs (norm_pairs_per_tile per tile) follow the previous
+// one's.
+hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, int store_lds_pad, hipStream_t s);
+// The update of n segments (all from gbar or none), likewise.
+// lds_pad: for one segment, segments_lds_pad: for several.
+hipError_t launch_update_segments(int R, const Segment *segs, int n, const UpdateConsts &c, int lds_pad,
+                                  int segments_lds_pad, hipStream_t s);
 // merged: room for ceil(n_pairs / kMergeRun) pairs (used when n_pairs > kMergeRun).
 hipError_t launch_norm_finalize(const double *partials /* pairs */, int64_t n_pairs, double *merged,
                                 double max_grad_norm, NormState *ns, hipStream_t s);
-hipError_t launch_update(int R, const UpdateArgs &a, int max_blocks, int lds_pad, hipStream_t s);
+hipError_t launch_update(int R, UpdateArgs a, int max_blocks, int lds_pad, hipStream_t s);
 hipError_t launch_gbar_out(int R, const GbarArgs &a, hipStream_t s);
 hipError_t launch_update_pattern(int R, const UpdateArgs &a, int lds_pad, hipStream_t s);
 hipError_t launch_norm_pattern(int R, const NormArgs &a, int store_lds_pad, hipStream_t s);

@@ -586,6 +586,60 @@ __global__ __launch_bounds__((NormShape<R, WRITE_GBAR>::kThreads)) void k_norm_p
     }
 }
 
+// ---------------------------------------------------------------------------
+// Several segments in one launch.  A call's segments are often small (the
+// tensors of a layer, the layers of a small model): a launch each left the
+// chip idle in every ragged last wave of blocks and 2-8 us between kernels,
+// and cost the host 2.3 us each.  Measured with one launch per segment and
+// with this one: nine tensors, 48M elements, R = 4, 400 and 356 us; 26
+// segments, 613M elements, R = 1, 3115 and 2832 us; four tensors of 231,084
+// elements in all, 70 and 37 us.
+template <int R>
+struct SegEntry {  // one run of scalar loads
+    int64_t end;    // first block after the segment
+    int64_t first;  // its first block
+    float *p, *m, *v;
+    uint16_t *pb;
+    float *gbar;
+    int64_t n;
+    const uint16_t *g[R];
+};
+
+// The segment of a block is looked up in a map of up to 256 runs of 2^shift
+// blocks, four one-byte entries per word: the segment of the run's first
+// block, from which the few blocks of later segments step on.  Two scalar
+// loads deep, against one for a single segment; comparing the block with
+// every segment's first one instead held each wave back by 0.3 us, 10% of
+// its life, and the update with it.
+constexpr int kSegMapRuns = 256;
+template <int R>
+struct SegTable {
+    static constexpr int kSegs = segs_per_launch(R);
+    uint32_t map[kSegMapRuns / 4];
+    uint32_t shift;
+    SegEntry<R> seg[kSegs];
+};
+
+template <int R>
+__device__ __forceinline__ const SegEntry<R> &segment_of(const SegTable<R> &t, uint32_t b) {
+    const uint32_t run = b >> t.shift;
+    uint32_t s = t.map[run / 4] >> (run % 4 * 8) & 0xffu;
+    while (__builtin_expect(b >= t.seg[s].end, 0)) ++s;
+    return t.seg[s];
+}
+
+template <int R, bool WRITE_GBAR>
+__global__ __launch_bounds__((NormShape<R, WRITE_GBAR>::kThreads)) void k_norm_segments(SegTable<R> t,
+                                                                                      double *partials) {
+    const SegEntry<R> &e = segment_of<R>(t, blockIdx.x);
+    double hi, lo;
+    norm_span<R, WRITE_GBAR, NormShape<R, WRITE_GBAR>>(e.g, e.n, blockIdx.x - e.first, e.gbar, hi, lo);
+    if (threadIdx.x == 0) {
+        partials[2 * (int64_t)blockIdx.x] = hi;
+        partials[2 * (int64_t)blockIdx.x + 1] = lo;
+    }
+}
+
 // First stage of the finalize for many pairs: block b merges the pairs
 // b*kMergeRun + t + kMergeThreads*j (j = 0 .. 7) in increasing j per thread,
 // then the threads by the fixed block tree, into merged pair b.  Pairs past
@@ -661,6 +715,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_norm_finalize(
 
 struct Consts {
     double c, lr_wd, beta1, omb1, beta2, omb2, step_size, inv_bc2, eps;
+    int nonfinite;
 };
 
 // p1, m' and v' are each rounded after every product and sum, in the order
@@ -689,15 +744,16 @@ __device__ __forceinline__ void adamw(float &p, float &m, float &v, float g_bar,
     v = (float)v1;
 }
 
-// Lane t of the grid handles elements 4t .. 4t+3: each access of a wave is
-// one contiguous run (1 KB of every FP32 array, 512 B of every BF16 one).
-// Every load and store is non-temporal: under the residency cap this
-// measured about 5% faster than plain accesses to the states and g_bar.
-template <int R, bool CACHED>
-__global__ __launch_bounds__(kUpdateThreads) void k_update(UpdateArgs a) {
-    const NormState *ns = a.ns;
-    if (ns->nonfinite) return;
+// The norm state comes through scalar loads (an earlier kernel wrote it and
+// no block of this one does).
+__device__ __forceinline__ Consts load_consts(const UpdateConsts &a) {
+    uintptr_t at = (uintptr_t)a.ns;
+    // behind the loads before it: waiting for the norm state first would add
+    // a memory latency to every wave
+    asm volatile("" : "+s"(at)::"memory");
+    const auto *ns = (const __attribute__((address_space(4))) NormState *)at;
     Consts k;
+    k.nonfinite = ns->nonfinite;
     k.c = ns->clip;
     k.lr_wd = a.lr_wd;
     k.beta1 = a.beta1;
@@ -707,59 +763,85 @@ __global__ __launch_bounds__(kUpdateThreads) void k_update(UpdateArgs a) {
     k.step_size = a.step_size;
     k.inv_bc2 = a.inv_bc2;
     k.eps = a.eps;
+    return k;
+}
 
-    float *__restrict__ P = a.p;
-    float *__restrict__ M = a.m;
-    float *__restrict__ V = a.v;
-    uint16_t *__restrict__ PB = a.pb;
-    const float *__restrict__ GB = a.gbar;
-    const int64_t n = a.n;
+// The 4-element groups q0, q0 + stride, ... of a segment, and, for q0 = 0, its
+// ragged tail of fewer than 4 elements.  Lane t of the grid handles elements
+// 4t .. 4t+3: each access of a wave is one contiguous run (1 KB of every FP32
+// array, 512 B of every BF16 one).
+// Every load and store is non-temporal: under the residency cap this
+// measured about 5% faster than plain accesses to the states and g_bar.
+template <int R, bool CACHED>
+__device__ __forceinline__ void update_groups(float *__restrict__ P, float *__restrict__ M, float *__restrict__ V,
+                                              uint16_t *__restrict__ PB, const uint16_t *const *grads,
+                                              const float *__restrict__ GB, int64_t n, int64_t q0, int64_t stride,
+                                              const UpdateConsts &a) {
     const int64_t groups = n / kUpdVec;
-    const int64_t gid = (int64_t)blockIdx.x * kUpdateThreads + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * kUpdateThreads;
-
-    for (int64_t q = gid; q < groups; q += stride) {
+    for (int64_t q = q0; q < groups; q += stride) {
         const int64_t e0 = q * kUpdVec;
-        float g[kUpdVec];
-        bool fast = true;
+        float4 gb;
+        uint32_t raw[R][2];
         if constexpr (CACHED) {
-            const float4 a0 = load_nt4(GB + e0);
-            g[0] = a0.x; g[1] = a0.y; g[2] = a0.z; g[3] = a0.w;
+            gb = load_nt4(GB + e0);
         } else {
-            uint32_t raw[R][2];
             // read once: non-temporal, as in the norm pass
 #pragma unroll
-            for (int r = 0; r < R; ++r) load_stream_v<4>(a.g[r] + e0, raw[r]);
-            fast = means_fast<R, 2>(raw, g);
+            for (int r = 0; r < R; ++r) load_stream_v<4>(grads[r] + e0, raw[r]);
         }
         float4 pv = load_nt4(P + e0);
         float4 mv = load_nt4(M + e0);
         float4 vv = load_nt4(V + e0);
-        if (__builtin_expect(!fast, 0)) {
-            // the wide route (see means_fast)
-            const float4 t = mean_wide_at4<R>(a.g, e0);
-            g[0] = t.x; g[1] = t.y; g[2] = t.z; g[3] = t.w;
+        const Consts k = load_consts(a);
+        float g[kUpdVec];
+        if constexpr (CACHED) {
+            g[0] = gb.x; g[1] = gb.y; g[2] = gb.z; g[3] = gb.w;
+        } else {
+            mean4<R>(raw, grads, e0, g);
         }
         float *pf = &pv.x, *mf = &mv.x, *vf = &vv.x;
 #pragma unroll
         for (int e = 0; e < kUpdVec; ++e) adamw(pf[e], mf[e], vf[e], g[e], k);
+        // a non-finite norm is acted on here and not before the loads, which
+        // would then wait for the norm state: the results pass through an
+        // empty statement, so that the compiler cannot move the branch up
+        int skip = k.nonfinite;
+        asm volatile("" : "+s"(skip) : "v"(pv.x), "v"(pv.y), "v"(pv.z), "v"(pv.w), "v"(mv.x), "v"(mv.y), "v"(mv.z),
+                     "v"(mv.w), "v"(vv.x), "v"(vv.y), "v"(vv.z), "v"(vv.w));
+        if (skip) return;
         store_nt4(P + e0, pv);
         store_nt4(M + e0, mv);
         store_nt4(V + e0, vv);
         store_nt2(PB + e0, pack_bf16(pf[0], pf[1]), pack_bf16(pf[2], pf[3]));
     }
-    // ragged tail of fewer than 4 elements
-    if (gid == 0) {
+    if (q0 == 0 && groups * kUpdVec < n) {
+        const Consts k = load_consts(a);
+        if (k.nonfinite) return;
         for (int64_t i = groups * kUpdVec; i < n; ++i) {
             float gb;
             if constexpr (CACHED) gb = GB[i];
-            else gb = mean1<R>(a.g, i);
+            else gb = mean1<R>(grads, i);
             float p = P[i], m = M[i], v = V[i];
             adamw(p, m, v, gb, k);
             P[i] = p; M[i] = m; V[i] = v;
             PB[i] = (uint16_t)bf16_rne(p);
         }
     }
+}
+
+template <int R, bool CACHED>
+__global__ __launch_bounds__(kUpdateThreads) void k_update(UpdateArgs a) {
+    update_groups<R, CACHED>(a.p, a.m, a.v, a.pb, a.g, a.gbar, a.n, (int64_t)blockIdx.x * kUpdateThreads + threadIdx.x,
+                             a.stride, a);
+}
+
+// The update of several segments: block b handles the 64 groups from
+// 64 * (b - first) of its segment.
+template <int R, bool CACHED>
+__global__ __launch_bounds__(kUpdateThreads) void k_update_segments(SegTable<R> t, UpdateConsts c) {
+    const SegEntry<R> &e = segment_of<R>(t, blockIdx.x);
+    const int64_t q0 = (blockIdx.x - e.first) * kUpdateThreads + threadIdx.x;
+    update_groups<R, CACHED>(e.p, e.m, e.v, e.pb, e.g, e.gbar, e.n, q0, (int64_t)1 << 62, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -959,6 +1041,103 @@ hipError_t update_r(const UpdateArgs &a, int64_t blocks, int lds_pad, hipStream_
     return hipGetLastError();
 }
 
+// Block counts of one segment in the batched launches.
+int64_t update_blocks(int64_t n) {
+    const int64_t b = cdiv(n / kUpdVec, kUpdateThreads);
+    return b < 1 ? 1 : b;
+}
+
+constexpr int64_t kMaxGrid = 0x7fffffff;
+
+// Fills `t` from segs[0 .. n): as many segments as fit the table and the
+// grid; returns how many, and the blocks they need.
+template <int R, class F>
+int fill_table(SegTable<R> &t, const Segment *segs, int n, bool cached_only, F blocks_of, int64_t *blocks) {
+    int k = 0;
+    *blocks = 0;
+    for (; k < n && k < SegTable<R>::kSegs; ++k) {
+        const int64_t b = blocks_of(segs[k].n);
+        if (k > 0 && *blocks + b > kMaxGrid) break;
+        SegEntry<R> &e = t.seg[k];
+        e.p = segs[k].p;
+        e.m = segs[k].m;
+        e.v = segs[k].v;
+        e.pb = segs[k].pb;
+        e.gbar = segs[k].gbar;
+        e.n = segs[k].n;
+        e.first = *blocks;
+        for (int r = 0; r < R && !cached_only; ++r) e.g[r] = segs[k].g[r];
+        *blocks += b;
+        e.end = *blocks;
+    }
+    while ((*blocks - 1) >> t.shift >= kSegMapRuns) ++t.shift;
+    for (int run = 0, at = 0; run < kSegMapRuns && (int64_t)run << t.shift < *blocks; ++run) {
+        while (t.seg[at].end <= (int64_t)run << t.shift) ++at;
+        t.map[run / 4] |= (uint32_t)at << (run % 4 * 8);
+    }
+    return k;
+}
+
+template <int R>
+hipError_t norm_segments_r(const Segment *segs, int n, double *partials, int store_lds_pad, hipStream_t s) {
+    const bool store = segs[0].gbar != nullptr;
+    const int ppt = norm_pairs_per_tile(R, store);
+    for (int k = 0; k < n;) {
+        if (n - k == 1) {
+            NormArgs a{};
+            for (int r = 0; r < R; ++r) a.g[r] = segs[k].g[r];
+            a.n = segs[k].n;
+            a.partials = partials;
+            a.gbar_out = segs[k].gbar;
+            return norm_r<R>(a, store_lds_pad, s);
+        }
+        SegTable<R> t{};
+        int64_t blocks = 0;
+        const int done = fill_table<R>(t, segs + k, n - k, false, [&](int64_t e) { return cdiv(e, kTile) * ppt; }, &blocks);
+        if (store)
+            hipLaunchKernelGGL((k_norm_segments<R, true>), dim3((uint32_t)blocks), dim3(NormShape<R, true>::kThreads),
+                               store_lds_pad, s, t, partials);
+        else
+            hipLaunchKernelGGL((k_norm_segments<R, false>), dim3((uint32_t)blocks), dim3(NormShape<R, false>::kThreads),
+                               0, s, t, partials);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        partials += 2 * blocks;
+        k += done;
+    }
+    return hipSuccess;
+}
+
+// R ranks, or (CACHED) the stored g_bar, where R = 1 stands for any number.
+template <int R, bool CACHED>
+hipError_t update_segments_r(const Segment *segs, int n, const UpdateConsts &c, int lds_pad, int segments_lds_pad,
+                             hipStream_t s) {
+    for (int k = 0; k < n;) {
+        if (n - k == 1) {
+            UpdateArgs a{};
+            static_cast<UpdateConsts &>(a) = c;
+            a.p = segs[k].p;
+            a.m = segs[k].m;
+            a.v = segs[k].v;
+            a.pb = segs[k].pb;
+            for (int r = 0; r < R && !CACHED; ++r) a.g[r] = segs[k].g[r];
+            a.gbar = segs[k].gbar;
+            a.n = segs[k].n;
+            a.stride = update_blocks(a.n) * kUpdateThreads;
+            return update_r<R>(a, update_blocks(a.n), lds_pad, s);
+        }
+        SegTable<R> t{};
+        int64_t blocks = 0;
+        const int done = fill_table<R>(t, segs + k, n - k, CACHED, update_blocks, &blocks);
+        hipLaunchKernelGGL((k_update_segments<R, CACHED>), dim3((uint32_t)blocks), dim3(kUpdateThreads),
+                           segments_lds_pad, s, t, c);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        k += done;
+    }
+    return hipSuccess;
+}
+
 template <int R>
 hipError_t pattern_r(const UpdateArgs &a, int64_t blocks, int lds_pad, hipStream_t s) {
     if (a.gbar)
@@ -997,6 +1176,26 @@ hipError_t launch_norm_partials(int R, const NormArgs &a, int store_lds_pad, hip
     }
 }
 
+hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, int store_lds_pad, hipStream_t s) {
+    switch (R) {
+#define CASE(r) case r: return norm_segments_r<r>(segs, n, partials, store_lds_pad, s);
+        SDP_FOR_EACH_R(CASE)
+#undef CASE
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_update_segments(int R, const Segment *segs, int n, const UpdateConsts &c, int lds_pad,
+                                  int segments_lds_pad, hipStream_t s) {
+    if (segs[0].gbar) return update_segments_r<1, true>(segs, n, c, lds_pad, segments_lds_pad, s);
+    switch (R) {
+#define CASE(r) case r: return update_segments_r<r, false>(segs, n, c, lds_pad, segments_lds_pad, s);
+        SDP_FOR_EACH_R(CASE)
+#undef CASE
+        default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_norm_finalize(const double *partials, int64_t n_partials, double *merged, double max_grad_norm,
                                 NormState *ns, hipStream_t s) {
     if (n_partials > kMergeRun) {
@@ -1014,10 +1213,10 @@ hipError_t launch_norm_finalize(const double *partials, int64_t n_partials, doub
     return hipGetLastError();
 }
 
-hipError_t launch_update(int R, const UpdateArgs &a, int max_blocks, int lds_pad, hipStream_t s) {
-    int64_t blocks = cdiv(a.n / kUpdVec, kUpdateThreads);
-    if (blocks < 1) blocks = 1;
+hipError_t launch_update(int R, UpdateArgs a, int max_blocks, int lds_pad, hipStream_t s) {
+    int64_t blocks = update_blocks(a.n);
     if (max_blocks > 0 && blocks > max_blocks) blocks = max_blocks;
+    a.stride = blocks * kUpdateThreads;
     switch (R) {
 #define CASE(r) case r: return update_r<r>(a, blocks, lds_pad, s);
         SDP_FOR_EACH_R(CASE)

@@ -29,7 +29,7 @@ namespace sdprt {
 int fail(int status, const char *fmt, ...);
 extern thread_local std::string t_err;
 int check_hparams(const sdp_adamw_params *hp);
-void fill_consts(const sdp_adamw_params *hp, sdp::UpdateArgs &a);
+void fill_consts(const sdp_adamw_params *hp, sdp::UpdateConsts &a);
 }  // namespace sdprt
 
 namespace {
@@ -62,6 +62,7 @@ struct DeviceSetup {
     bool ready = false;
     unsigned char *ptr = nullptr;  // scratch on this device
     int update_lds_pad = 0;        // the fused update's residency cap, as a context sets it
+    int update_segments_lds_pad = 0;
 };
 
 std::mutex g_setup_mu;
@@ -85,10 +86,14 @@ int setup_device(int device, DeviceSetup *out) {
             (void)hipGetLastError();
             return fail(SDP_ERR_HIP, "cannot query the LDS size of GPU %d", device);
         }
-        // the same cap as a context's default: the compute unit's LDS over
-        // kUpdateBlocksPerCU blocks, through dynamic LDS the kernel never uses
-        const int pad = (lds_cu / sdp::kUpdateBlocksPerCU) / 1024 * 1024;
-        d.update_lds_pad = pad > 0 && pad <= lds_block ? pad : 0;
+        // the same caps as a context's defaults: the compute unit's LDS over
+        // so many blocks, through dynamic LDS the kernels never use
+        auto pad_for = [&](int blocks) {
+            const int pad = (lds_cu / blocks) / 1024 * 1024;
+            return pad > 0 && pad <= lds_block ? pad : 0;
+        };
+        d.update_lds_pad = pad_for(sdp::kUpdateBlocksPerCU);
+        d.update_segments_lds_pad = pad_for(sdp::kUpdateSegmentsBlocksPerCU);
         d.ptr = (unsigned char *)p;
         d.ready = true;
     }
@@ -211,34 +216,19 @@ int sdp_agg_adam_step_noalloc(const sdp_segment *segs, int32_t n_segs, const sdp
         }                                                                                              \
     } while (0)
     // norm pass over every tile of every segment, in segment then tile order
+    sdp::Segment ks[SDP_NOALLOC_MAX_SEGMENTS];
+    for (int32_t s = 0; s < n_segs; ++s)
+        ks[s] = {segs[s].master, segs[s].exp_avg, segs[s].exp_avg_sq, segs[s].param_bf16, segs[s].grads, nullptr,
+                 segs[s].numel};
+    NA_HIP(sdp::launch_norm_segments(R, ks, n_segs, partials, 0, st));
     const int64_t ppt = sdp::norm_pairs_per_tile(R, false);  // at most kMaxPairs / kMaxTiles
-    int64_t tile_base = 0;
-    for (int32_t s = 0; s < n_segs; ++s) {
-        sdp::NormArgs a{};
-        for (int32_t r = 0; r < R; ++r) a.g[r] = segs[s].grads[r];
-        a.n = segs[s].numel;
-        a.partials = partials + 2 * ppt * tile_base;
-        a.gbar_out = nullptr;
-        NA_HIP(sdp::launch_norm_partials(R, a, 0, st));
-        tile_base += (segs[s].numel / SDP_NORM_TILE + (segs[s].numel % SDP_NORM_TILE != 0));
-    }
     NA_HIP(sdp::launch_norm_finalize(partials, tiles * ppt, merged, hp->max_grad_norm, ns, st));
     // the fused update, reading the clip coefficient from the norm state,
     // with the per-step constants computed as for every other mode
-    for (int32_t s = 0; s < n_segs; ++s) {
-        const sdp_segment &g = segs[s];
-        sdp::UpdateArgs a{};
-        a.p = g.master;
-        a.m = g.exp_avg;
-        a.v = g.exp_avg_sq;
-        a.pb = g.param_bf16;
-        for (int32_t r = 0; r < R; ++r) a.g[r] = g.grads[r];
-        a.gbar = nullptr;
-        a.n = g.numel;
-        a.ns = ns;
-        sdprt::fill_consts(hp, a);
-        NA_HIP(sdp::launch_update(R, a, 0, dev.update_lds_pad, st));
-    }
+    sdp::UpdateConsts c{};
+    c.ns = ns;
+    sdprt::fill_consts(hp, c);
+    NA_HIP(sdp::launch_update_segments(R, ks, n_segs, c, dev.update_lds_pad, dev.update_segments_lds_pad, st));
     if (grad_norm_out) {
         sdp::NormState hs{};
         NA_HIP(hipMemcpyAsync(&hs, ns, sizeof hs, hipMemcpyDeviceToHost, st));

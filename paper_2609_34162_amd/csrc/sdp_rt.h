@@ -262,6 +262,7 @@ struct sdp_ctx {
     sdp::NormState *ns_host = nullptr;  // pinned mirror for read-back
     int update_max_blocks = 0;     // 0: one 8-element group per lane
     int update_lds_pad = 0;        // dynamic LDS bytes per update block (residency cap); 0: no cap
+    int update_segments_lds_pad = 0;  // the same for the update of several segments
     int norm_store_blocks = -1;    // SDP_NORM_STORE_BLOCKS_PER_CU, or -1: norm_store_blocks_per_cu(R)
     int lds_cu = 0, lds_block = 0;  // LDS bytes of a compute unit, and the most that a block may have
     bool timing = false;
@@ -319,7 +320,7 @@ int norm_store_lds_pad(const sdp_ctx *ctx, int32_t R);
 int norm_launch(sdp_ctx *ctx, int32_t R, const uint16_t *const *g, int64_t n, double *partials, float *gbar_out,
                 hipStream_t s);
 int finalize_launch(sdp_ctx *ctx, int64_t pairs, double max_grad_norm, hipStream_t s);
-void fill_consts(const sdp_adamw_params *hp, sdp::UpdateArgs &a);
+void fill_consts(const sdp_adamw_params *hp, sdp::UpdateConsts &a);
 int update_launch(sdp_ctx *ctx, int32_t R, const sdp_adamw_params *hp, float *p, float *m, float *v, uint16_t *pb,
                   const uint16_t *const *g, const float *gbar, int64_t n, hipStream_t s);
 int order_after_last(sdp_ctx *ctx, hipStream_t s);

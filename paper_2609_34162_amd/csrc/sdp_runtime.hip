@@ -5,9 +5,10 @@
 // sdp_kernels.hip, the host AdamW lane in sdp_host_adamw.cpp and the
 // step-time model in sdp_schedule.cpp.
 //
-// Device mode (sdp_agg_adam_step): per call, one norm-partials launch per
-// segment, the finalize (one launch, or two above 2,048 span partials) and
-// one fused-update launch per segment, all on the caller's stream.  The clip
+// Device mode (sdp_agg_adam_step): per call, one norm-partials launch, the
+// finalize (one launch, or two above 2,048 span partials) and one fused-update
+// launch, all on the caller's stream (for more segments than a launch takes,
+// 19 to 32 by the number of ranks, one for each so many).  The clip
 // coefficient stays in device memory.
 #include "sdp_rt.h"
 #include "sdp_schedule.h"
@@ -325,7 +326,7 @@ int finalize_launch(sdp_ctx *ctx, int64_t pairs, double max_grad_norm, hipStream
     return SDP_OK;
 }
 
-void fill_consts(const sdp_adamw_params *hp, sdp::UpdateArgs &a) {
+void fill_consts(const sdp_adamw_params *hp, sdp::UpdateConsts &a) {
     const double t = (double)hp->step;
     const double bc1 = 1.0 - std::pow(hp->beta1, t);
     const double bc2 = 1.0 - std::pow(hp->beta2, t);
@@ -411,13 +412,55 @@ int sync_streams(sdp_ctx *ctx) {
 
 // ---- device mode ----------------------------------------------------------
 
+namespace {
+std::vector<sdp::Segment> kernel_segments(const sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs,
+                                          const Plan &plan, bool stored_gbar) {
+    std::vector<sdp::Segment> out;
+    out.reserve((size_t)n_segs);
+    for (int32_t k = 0; k < n_segs; ++k) {
+        const sdp_segment &g = segs[k];
+        out.push_back({g.master, g.exp_avg, g.exp_avg_sq, g.param_bf16, g.grads,
+                       stored_gbar ? ctx->gbar + plan.gbar_base[k] : nullptr, g.numel});
+    }
+    return out;
+}
+
+int64_t total_elems(const sdp_segment *segs, int32_t n_segs) {
+    int64_t n = 0;
+    for (int32_t k = 0; k < n_segs; ++k) n += segs[k].numel;
+    return n;
+}
+}  // namespace
+
 int device_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool store_gbar,
                 double max_grad_norm, hipStream_t s) {
     const int ppt = sdp::norm_pairs_per_tile(R, store_gbar);
-    for (int32_t k = 0; k < n_segs; ++k)
-        SDP_TRY(norm_launch(ctx, R, segs[k].grads, segs[k].numel, tile_partials(ctx, plan.tile_base[k], ppt),
-                            store_gbar ? ctx->gbar + plan.gbar_base[k] : nullptr, s));
+    const std::vector<sdp::Segment> ks = kernel_segments(ctx, segs, n_segs, plan, store_gbar);
+    hipEvent_t t0 = timed_begin(ctx, s);
+    HIP_TRY(sdp::launch_norm_segments(R, ks.data(), n_segs, ctx->partials, norm_store_lds_pad(ctx, R), s));
+    timed_end(ctx, s, t0, kNorm, total_elems(segs, n_segs));
     return finalize_launch(ctx, plan.tiles * ppt, max_grad_norm, s);
+}
+
+int device_update(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool stored_gbar,
+                  const sdp_adamw_params *hp, hipStream_t s) {
+    // a cap on the blocks of a launch: one launch per segment
+    if (ctx->update_max_blocks > 0) {
+        for (int32_t k = 0; k < n_segs; ++k) {
+            const sdp_segment &g = segs[k];
+            SDP_TRY(update_launch(ctx, R, hp, g.master, g.exp_avg, g.exp_avg_sq, g.param_bf16, g.grads,
+                                  stored_gbar ? ctx->gbar + plan.gbar_base[k] : nullptr, g.numel, s));
+        }
+        return SDP_OK;
+    }
+    const std::vector<sdp::Segment> ks = kernel_segments(ctx, segs, n_segs, plan, stored_gbar);
+    sdp::UpdateConsts c{};
+    c.ns = ctx->ns;
+    fill_consts(hp, c);
+    hipEvent_t t0 = timed_begin(ctx, s);
+    HIP_TRY(sdp::launch_update_segments(R, ks.data(), n_segs, c, ctx->update_lds_pad, ctx->update_segments_lds_pad, s));
+    timed_end(ctx, s, t0, kUpdate, total_elems(segs, n_segs));
+    return SDP_OK;
 }
 
 // ---- chunks and staging slots -------------------------------------------
@@ -742,6 +785,8 @@ int sdp_ctx_create(sdp_ctx **out, int device, int64_t max_chunk_elems, int32_t m
         c->lds_cu = lds_cu;
         c->lds_block = lds_block;
         c->update_lds_pad = residency_pad(c, from_env("SDP_UPDATE_BLOCKS_PER_CU", sdp::kUpdateBlocksPerCU), 0);
+        c->update_segments_lds_pad =
+            residency_pad(c, from_env("SDP_UPDATE_BLOCKS_PER_CU", sdp::kUpdateSegmentsBlocksPerCU), 0);
         c->norm_store_blocks = from_env("SDP_NORM_STORE_BLOCKS_PER_CU", -1);
     }
 #define CTX_HIP(expr)                                                                                \
@@ -869,11 +914,7 @@ int sdp_agg_adam_step(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, con
     hipStream_t s = (hipStream_t)stream;
     SDP_TRY(order_after_last(ctx, s));
     SDP_TRY(device_norm(ctx, segs, n_segs, R, plan, store, hp->max_grad_norm, s));
-    for (int32_t k = 0; k < n_segs; ++k) {
-        const sdp_segment &g = segs[k];
-        SDP_TRY(update_launch(ctx, R, hp, g.master, g.exp_avg, g.exp_avg_sq, g.param_bf16, g.grads,
-                              store ? ctx->gbar + plan.gbar_base[k] : nullptr, g.numel, s));
-    }
+    SDP_TRY(device_update(ctx, segs, n_segs, R, plan, store, hp, s));
     SDP_TRY(mark_done(ctx, s));
     if (grad_norm_out) {
         NormState st;

@@ -49,3 +49,32 @@ def test_norm_bits_at_span_edges(sdp, R, store):
                 check_state(dev.host(), ref)
     finally:
         sdp.sdp_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("R", [1, 3, 4, 8, 16])
+@pytest.mark.parametrize("count", [2, 19, 33, 64])
+def test_many_segments(sdp, R, count):
+    """Calls around the number of segments that one launch takes (19 to 32, by
+    the rank count), with sizes around a lane's group, a block's groups and
+    spans: device mode and the no-allocation entry point against the oracle."""
+    log(f"many segments R={R} count={count}")
+    sizes = [[1, 3, 4, 255, 256, 257, 1027, 4096, 5000, 8193, 20000][k % 11] for k in range(count)]
+    sizes[count // 2] = 65536 + 5
+    masters, grads = rand_inputs(sizes, R, 1, seed=7 * count + R)
+    hs, ho = hp_pair(sdp, lr=1e-3, weight_decay=0.02, max_grad_norm=0.05, step=2)
+    ref = oracle.State(masters)
+    _, onorm = oracle.step(ref, grads[0], ho)
+    s = torch.cuda.current_stream()
+    ctx = sdp.sdp_ctx_create(0, 0, R, 0)
+    try:
+        for noalloc in (False, True):
+            dev = DevState(masters, R)
+            dev.set_grads(grads[0])
+            if noalloc:
+                norm = sdp.sdp_agg_adam_step_noalloc(dev.segments(sdp), hs, s, want_norm=True)
+            else:
+                norm = sdp.sdp_agg_adam_step(ctx, dev.segments(sdp), hs, 0, s, want_norm=True)
+            assert norm == onorm, (noalloc, norm, onorm)
+            check_state(dev.host(), ref)
+    finally:
+        sdp.sdp_ctx_destroy(ctx)

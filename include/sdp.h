@@ -166,7 +166,7 @@ typedef struct {
  * each launch on the stream the launch uses (only while timing is on). */
 typedef struct {
     double norm_ms;       /* norm-partials kernel (first pass over the gradients) */
-    double finalize_ms;   /* norm finalize (both of its kernels, one launch each) */
+    double finalize_ms;   /* norm finalize (while timing is on always a launch of its own) */
     double update_ms;     /* fused aggregate + clip + AdamW + BF16 kernel */
     int64_t norm_launches, finalize_launches, update_launches;
     int64_t update_elems; /* elements processed by the timed update launches */
@@ -207,9 +207,9 @@ SDP_API void sdp_ctx_destroy(sdp_ctx *ctx);
  * before it has no counterpart in the paper.  All state and gradient buffers
  * are device memory of ctx's GPU.  Enqueues on `stream`: the norm pass over every tile of every segment
  * (segment order, then tile order), the norm finalize (a fixed-order merge of
- * the span partials, in two stages above 2,048 of them), and the
- * fused update over every element; the update reads the clip coefficient and
- * the non-finite flag from device memory, so nothing returns to the host.
+ * the span partials; up to 256 of them the update merges itself), and the
+ * fused update over every element; the update has the clip coefficient and
+ * the non-finite flag from device memory, so it waits for nothing on the host.
  * chunk_elems (0 or a multiple of SDP_NORM_TILE) names the unit the caller
  * works in; results never depend on it, and one launch per kernel covers up to
  * 19 to 32 segments (by the number of ranks).  Asynchronous unless grad_norm_out is non-NULL: then the
@@ -225,7 +225,7 @@ SDP_API int sdp_agg_adam_step(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_s
 /* Device mode for callers that cannot allocate: code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation.  As
  * sdp_agg_adam_step on the GPU current to the calling thread, with no
- * context: the norm partials, the finalize's merge stage and the norm state
+ * context: the norm partials, the finalize's merged pairs and the norm state
  * live in a static device array of the library (4 MiB on each GPU it runs
  * on, held until the process ends; its address on a GPU is looked up on the
  * first call there).  The call allocates nothing, host or device.  The mean

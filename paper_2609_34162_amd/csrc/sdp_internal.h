@@ -16,7 +16,18 @@ struct NormState {
     double norm;
     double clip;
     int32_t nonfinite;
-    int32_t pad;
+    uint32_t arrived;  // blocks of the finalize that have merged their pairs (the norm pass clears it)
+};
+
+// Where the span pairs of a call lie and what to do with their sum: from them
+// the finalize makes the norm state, or, for up to kFoldPairs of them, the
+// update itself.
+struct NormSum {
+    const double *pairs;
+    int64_t n_pairs;
+    double max_grad_norm;
+    NormState *ns;      // written
+    NormState *mirror;  // NULL, or pinned host memory written too
 };
 
 // One launch of the norm pass: `n` elements starting at a tile boundary of
@@ -30,10 +41,12 @@ struct NormArgs {
     int64_t n;
     double *partials;
     float *gbar_out;
+    NormState *ns;  // its arrival count is cleared
 };
 
-// What an update needs beside its segment: the norm state and the per-step
-// constants, computed once on the host in FP64.
+// What an update needs beside its segment: the norm state, or the span pairs
+// that it sums itself (sum.n_pairs > 0), and the per-step constants, computed
+// once on the host in FP64.
 struct UpdateConsts {
     const NormState *ns;
     double lr_wd;      // lr * weight_decay
@@ -42,6 +55,7 @@ struct UpdateConsts {
     double step_size;  // lr / (1 - beta1^t)
     double inv_bc2;    // 1 / (1 - beta2^t)
     double eps;
+    NormSum sum;
 };
 
 // One launch of the fused update over `n` elements.  Gradients come either
@@ -124,12 +138,19 @@ constexpr int norm_pairs_per_tile(int R, bool store) {
     return kTile / (store ? (R > 4 ? NormShape<5, true>::kSpan : NormShape<1, true>::kSpan)
                           : (R == 1 ? NormShape<1, false>::kSpan : NormShape<2, false>::kSpan));
 }
-constexpr int kFinalizeThreads = 1024;
-// More than kMergeRun span pairs are merged in two fixed stages: block b of
-// k_norm_merge merges pairs b*kMergeRun .. (b+1)*kMergeRun - 1 into pair b
-// of a second array, and the one-block finalize merges those.
-constexpr int kMergeThreads = 256;
+// The finalize: blocks of kFinalizeThreads merge runs of a multiple of kMergeRun
+// pairs each, and the last block to arrive merges their results, so that it is
+// one launch at any size: 4.7 us where two launches took 9 (47,104 pairs).  At
+// most kMaxMergeBlocks blocks: they count themselves in one after the other,
+// about 33 ns apiece (1,675 blocks took 56 us).
+constexpr int kFinalizeThreads = 512;
 constexpr int kMergeRun = 2048;
+constexpr int kMaxMergeBlocks = 128;
+// Up to this many pairs every wave of the update sums them itself, behind its
+// loads, which saves the finalize's launch: four pairs per lane.  1M elements,
+// R = 2 (256 pairs): 18.9 us per step with the finalize, 14.6 without.  Beyond
+// it the sum would be repeated by too many waves.
+constexpr int kFoldPairs = 256;
 constexpr int kUpdateThreads = 64;
 // Fused update residency: blocks of one wave, at most kUpdateBlocksPerCU of
 // them per compute unit (two or three waves per SIMD).  The update's mix of
@@ -161,14 +182,14 @@ hipError_t launch_norm_partials(int R, const NormArgs &a, int store_lds_pad, hip
 // as their arguments allow.  partials: the first pair of the first segment;
 // each segment's pairs (norm_pairs_per_tile per tile) follow the previous
 // one's.
-hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, int store_lds_pad, hipStream_t s);
+hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, NormState *ns, int store_lds_pad,
+                                hipStream_t s);
 // The update of n segments (all from gbar or none), likewise.
 // lds_pad: for one segment, segments_lds_pad: for several.
 hipError_t launch_update_segments(int R, const Segment *segs, int n, const UpdateConsts &c, int lds_pad,
                                   int segments_lds_pad, hipStream_t s);
-// merged: room for ceil(n_pairs / kMergeRun) pairs (used when n_pairs > kMergeRun).
-hipError_t launch_norm_finalize(const double *partials /* pairs */, int64_t n_pairs, double *merged,
-                                double max_grad_norm, NormState *ns, hipStream_t s);
+// merged: room for kMaxMergeBlocks pairs (used when n_pairs > kMergeRun).
+hipError_t launch_norm_finalize(const NormSum &sum, double *merged, hipStream_t s);
 hipError_t launch_update(int R, UpdateArgs a, int max_blocks, int lds_pad, hipStream_t s);
 hipError_t launch_gbar_out(int R, const GbarArgs &a, hipStream_t s);
 hipError_t launch_update_pattern(int R, const UpdateArgs &a, int lds_pad, hipStream_t s);

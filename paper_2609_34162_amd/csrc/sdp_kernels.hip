@@ -1,6 +1,5 @@
-// gfx950 kernels of the data-parallel update: norm partials over fixed tiles,
-// a fixed-order finalize (one block, after a merge stage for many partials),
-// and the fused aggregate + clip + AdamW + BF16 re-emit pass.  All of them
+// gfx950 kernels of the data-parallel update: norm partials over fixed spans,
+// a fixed-order finalize, and the fused aggregate + clip + AdamW + BF16 re-emit pass.  All of them
 // are bound by HBM bandwidth and use no MFMA.
 // Their lanes move wide accesses: 16-byte (dwordx4) FP32 accesses throughout,
 // and BF16 in 16-byte or 8-byte pieces (eight or four elements per lane).
@@ -334,15 +333,6 @@ __device__ __forceinline__ void dd_add(double &hi, double &lo, double x) {
     lo += e;
 }
 
-__device__ __forceinline__ void dd_merge(double &hi, double &lo, double bhi, double blo) {
-    const double s = hi + bhi;
-    const double bb = s - hi;
-    double e = (hi - (s - bb)) + (bhi - bb);
-    e += lo + blo;
-    hi = s + e;           // renormalised: hi is the pair rounded to FP64
-    lo = e - (hi - s);
-}
-
 // The lane's partner in step STEP of the butterfly: lane ^ 1, lane ^ 2, then
 // (the quads being uniform by then) the mirrored lane of the half row and of
 // the row, lane ^ 16 and lane ^ 32.  The first four are register moves within
@@ -398,6 +388,7 @@ template <int THREADS>
 __device__ __forceinline__ void block_merge(double &hi, double &lo) {
     if constexpr (THREADS > 64) {
         __shared__ double2 pairs[THREADS - 64];
+        __syncthreads();  // an earlier call's pairs have been read
         if (threadIdx.x >= 64) pairs[threadIdx.x - 64] = make_double2(hi, lo);
         __syncthreads();
         if (threadIdx.x >= 64) return;
@@ -583,6 +574,7 @@ __global__ __launch_bounds__((NormShape<R, WRITE_GBAR>::kThreads)) void k_norm_p
     if (threadIdx.x == 0) {
         a.partials[2 * blockIdx.x] = hi;
         a.partials[2 * blockIdx.x + 1] = lo;
+        if (blockIdx.x == 0) a.ns->arrived = 0;
     }
 }
 
@@ -630,83 +622,100 @@ __device__ __forceinline__ const SegEntry<R> &segment_of(const SegTable<R> &t, u
 
 template <int R, bool WRITE_GBAR>
 __global__ __launch_bounds__((NormShape<R, WRITE_GBAR>::kThreads)) void k_norm_segments(SegTable<R> t,
-                                                                                      double *partials) {
+                                                                                      double *partials,
+                                                                                      NormState *ns) {
     const SegEntry<R> &e = segment_of<R>(t, blockIdx.x);
     double hi, lo;
     norm_span<R, WRITE_GBAR, NormShape<R, WRITE_GBAR>>(e.g, e.n, blockIdx.x - e.first, e.gbar, hi, lo);
     if (threadIdx.x == 0) {
         partials[2 * (int64_t)blockIdx.x] = hi;
         partials[2 * (int64_t)blockIdx.x + 1] = lo;
+        if (blockIdx.x == 0) ns->arrived = 0;
     }
 }
 
-// First stage of the finalize for many pairs: block b merges the pairs
-// b*kMergeRun + t + kMergeThreads*j (j = 0 .. 7) in increasing j per thread,
-// then the threads by the fixed block tree, into merged pair b.  Pairs past
-// the end count as zero.
-__global__ __launch_bounds__(kMergeThreads) void k_norm_merge(const double *__restrict__ partials,
-                                                              int64_t n_pairs, double *__restrict__ merged) {
-    constexpr int kPer = kMergeRun / kMergeThreads;
-    const double2 *pairs = reinterpret_cast<const double2 *>(partials);
-    const int64_t base = (int64_t)blockIdx.x * kMergeRun + threadIdx.x;
-    double2 b[kPer];
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const int64_t i = base + (int64_t)j * kMergeThreads;
-        b[j] = i < n_pairs ? pairs[i] : make_double2(0.0, 0.0);
+// ---------------------------------------------------------------------------
+// The norm from the span pairs.
+
+// The norm state of the sum of squares hi + lo, written where it is wanted.
+__device__ __forceinline__ NormState norm_state(double hi, double lo, double max_grad_norm) {
+    NormState st;
+    st.sumsq = hi + lo;
+    st.norm = sqrt(st.sumsq);
+    st.nonfinite = !isfinite(st.sumsq);
+    st.clip = 1.0;
+    if (max_grad_norm > 0.0 && !st.nonfinite) {
+        st.clip = max_grad_norm / (st.norm + 1e-6);
+        if (st.clip > 1.0) st.clip = 1.0;
     }
-    double hi = b[0].x, lo = b[0].y;
-#pragma unroll
-    for (int j = 1; j < kPer; ++j) dd_merge(hi, lo, b[j].x, b[j].y);
-    block_merge<kMergeThreads>(hi, lo);
-    if (threadIdx.x == 0) {
-        merged[2 * blockIdx.x] = hi;
-        merged[2 * blockIdx.x + 1] = lo;
-    }
+    st.arrived = 0;
+    return st;
 }
 
-// One block: fixed-order sum of all span partials (pairs), then the norm, the
-// clip coefficient and the non-finite flag.  Thread t takes the pairs
-// t + 1024*j; pair j goes to the thread's accumulator j mod 4 (four
-// independent chains), each merged in increasing j, and the four are then
-// merged in order.  Loads are issued 16 at a time so that their latencies
-// overlap.
-__global__ __launch_bounds__(kFinalizeThreads) void k_norm_finalize(
-    const double *__restrict__ partials, int64_t n_partials, double max_grad_norm,
-    NormState *__restrict__ ns) {
-    constexpr int kBatch = 16;
-    constexpr int kChains = 4;
-    const double2 *pairs = reinterpret_cast<const double2 *>(partials);
-    double chi[kChains] = {0.0, 0.0, 0.0, 0.0}, clo[kChains] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t i0 = threadIdx.x; i0 < n_partials; i0 += (int64_t)kBatch * kFinalizeThreads) {
-        double2 b[kBatch];
+// Sum of up to kFoldPairs pairs by one wave, the same bits in every lane: lane
+// l adds pairs l, l + 64, l + 128, l + 192, then the butterfly.
+__device__ __forceinline__ void fold_pairs(const double *pairs, int64_t n_pairs, double &hi, double &lo) {
+    const double2 *p = reinterpret_cast<const double2 *>(pairs);
+    const int lane = threadIdx.x & 63;
+    double2 b[kFoldPairs / 64];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int64_t i = i0 + (int64_t)u * kFinalizeThreads;
-            b[u] = i < n_partials ? pairs[i] : make_double2(0.0, 0.0);
+    for (int k = 0; k < kFoldPairs / 64; ++k)
+        b[k] = k * 64 + lane < n_pairs ? p[k * 64 + lane] : make_double2(0.0, 0.0);
+    hi = b[0].x;
+    lo = b[0].y;
+#pragma unroll
+    for (int k = 1; k < kFoldPairs / 64; ++k) dd_add_pair(hi, lo, b[k].x, b[k].y);
+    wave_merge(hi, lo);
+}
+
+// Up to kFoldPairs pairs: one wave, as the update does.  Up to kMergeRun: one
+// block.  More: block b merges the `run` pairs from b * run (a multiple of
+// kMergeRun), thread t of it t + kFinalizeThreads * j in increasing j, into
+// merged pair b, and the last block to arrive merges those in the same way; no
+// block waits for another.
+// The merged pairs and the count pass between blocks on different XCDs, so
+// they move by device-scope atomics.  Bound by the latency of its loads and of
+// the few dependent steps, not by any rate.
+__global__ __launch_bounds__(kFinalizeThreads) void k_norm_finalize(NormSum sum, int64_t run,
+                                                                      double *__restrict__ merged) {
+    constexpr int T = kFinalizeThreads;
+    double hi = 0.0, lo = 0.0;
+    if (sum.n_pairs <= kFoldPairs) {
+        if (threadIdx.x >= 64) return;
+        fold_pairs(sum.pairs, sum.n_pairs, hi, lo);
+    } else {
+        const double2 *p = reinterpret_cast<const double2 *>(sum.pairs);
+        for (int64_t at = 0; at < run; at += kMergeRun) {
+            const int64_t base = (int64_t)blockIdx.x * run + at + threadIdx.x;
+            double2 b[kMergeRun / T];
+#pragma unroll
+            for (int j = 0; j < kMergeRun / T; ++j)
+                b[j] = base + j * T < sum.n_pairs ? p[base + j * T] : make_double2(0.0, 0.0);
+#pragma unroll
+            for (int j = 0; j < kMergeRun / T; ++j) dd_add_pair(hi, lo, b[j].x, b[j].y);
         }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-            if (i0 + (int64_t)u * kFinalizeThreads < n_partials) dd_merge(chi[u % kChains], clo[u % kChains], b[u].x, b[u].y);
+        block_merge<T>(hi, lo);
+        if (gridDim.x > 1) {
+            __shared__ bool last;
+            if (threadIdx.x == 0) {
+                __hip_atomic_store(merged + 2 * blockIdx.x, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(merged + 2 * blockIdx.x + 1, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                last = __hip_atomic_fetch_add(&sum.ns->arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+                       gridDim.x - 1;
+            }
+            __syncthreads();
+            if (!last) return;
+            hi = lo = 0.0;
+            for (uint32_t i = threadIdx.x; i < gridDim.x; i += T)
+                dd_add_pair(hi, lo, __hip_atomic_load(merged + 2 * i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                            __hip_atomic_load(merged + 2 * i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            block_merge<T>(hi, lo);
+        }
     }
-    double hi = chi[0], lo = clo[0];
-#pragma unroll
-    for (int c = 1; c < kChains; ++c) dd_merge(hi, lo, chi[c], clo[c]);
-    block_merge<kFinalizeThreads>(hi, lo);
     if (threadIdx.x == 0) {
-        const double S = hi + lo;
-        const double norm = sqrt(S);
-        const int bad = !isfinite(S);
-        double c = 1.0;
-        if (max_grad_norm > 0.0 && !bad) {
-            c = max_grad_norm / (norm + 1e-6);
-            if (c > 1.0) c = 1.0;
-        }
-        ns->sumsq = S;
-        ns->norm = norm;
-        ns->clip = c;
-        ns->nonfinite = bad;
-        ns->pad = 0;
+        const NormState st = norm_state(hi, lo, sum.max_grad_norm);
+        *sum.ns = st;
+        if (sum.mirror) *sum.mirror = st;
     }
 }
 
@@ -745,16 +754,31 @@ __device__ __forceinline__ void adamw(float &p, float &m, float &v, float g_bar,
 }
 
 // The norm state comes through scalar loads (an earlier kernel wrote it and
-// no block of this one does).
+// no block of this one does), or (FOLD) the wave sums the span pairs itself,
+// and the grid's first wave writes the norm state.  All lanes of the wave call
+// it together.
+template <bool FOLD>
 __device__ __forceinline__ Consts load_consts(const UpdateConsts &a) {
-    uintptr_t at = (uintptr_t)a.ns;
-    // behind the loads before it: waiting for the norm state first would add
-    // a memory latency to every wave
-    asm volatile("" : "+s"(at)::"memory");
-    const auto *ns = (const __attribute__((address_space(4))) NormState *)at;
     Consts k;
-    k.nonfinite = ns->nonfinite;
-    k.c = ns->clip;
+    if constexpr (FOLD) {
+        double hi, lo;
+        fold_pairs(a.sum.pairs, a.sum.n_pairs, hi, lo);
+        const NormState st = norm_state(hi, lo, a.sum.max_grad_norm);
+        k.c = st.clip;
+        k.nonfinite = __builtin_amdgcn_readfirstlane(st.nonfinite);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            *a.sum.ns = st;
+            if (a.sum.mirror) *a.sum.mirror = st;
+        }
+    } else {
+        uintptr_t at = (uintptr_t)a.ns;
+        // behind the loads before it: waiting for the norm state first would
+        // add a memory latency to every wave
+        asm volatile("" : "+s"(at)::"memory");
+        const auto *ns = (const __attribute__((address_space(4))) NormState *)at;
+        k.nonfinite = ns->nonfinite;
+        k.c = ns->clip;
+    }
     k.lr_wd = a.lr_wd;
     k.beta1 = a.beta1;
     k.omb1 = a.one_minus_beta1;
@@ -766,57 +790,66 @@ __device__ __forceinline__ Consts load_consts(const UpdateConsts &a) {
     return k;
 }
 
-// The 4-element groups q0, q0 + stride, ... of a segment, and, for q0 = 0, its
-// ragged tail of fewer than 4 elements.  Lane t of the grid handles elements
-// 4t .. 4t+3: each access of a wave is one contiguous run (1 KB of every FP32
-// array, 512 B of every BF16 one).
+// One wave's part of a segment: lane l takes the 4-element groups w0 + l,
+// w0 + stride + l, ..., and lane 0 of the segment's first wave its ragged tail
+// of fewer than 4 elements.  Each access of the wave is one contiguous run
+// (1 KB of every FP32 array, 512 B of every BF16 one).
 // Every load and store is non-temporal: under the residency cap this
 // measured about 5% faster than plain accesses to the states and g_bar.
-template <int R, bool CACHED>
+template <int R, bool CACHED, bool FOLD>
 __device__ __forceinline__ void update_groups(float *__restrict__ P, float *__restrict__ M, float *__restrict__ V,
                                               uint16_t *__restrict__ PB, const uint16_t *const *grads,
-                                              const float *__restrict__ GB, int64_t n, int64_t q0, int64_t stride,
+                                              const float *__restrict__ GB, int64_t n, int64_t w0, int64_t stride,
                                               const UpdateConsts &a) {
     const int64_t groups = n / kUpdVec;
-    for (int64_t q = q0; q < groups; q += stride) {
-        const int64_t e0 = q * kUpdVec;
-        float4 gb;
+    const int lane = threadIdx.x & 63;
+    Consts k;
+    for (int64_t w = w0;;) {
+        const bool has = w + lane < groups;
+        const int64_t e0 = (w + lane) * kUpdVec;
+        float4 gb, pv, mv, vv;
         uint32_t raw[R][2];
-        if constexpr (CACHED) {
-            gb = load_nt4(GB + e0);
-        } else {
-            // read once: non-temporal, as in the norm pass
+        if (has) {
+            if constexpr (CACHED) {
+                gb = load_nt4(GB + e0);
+            } else {
+                // read once: non-temporal, as in the norm pass
 #pragma unroll
-            for (int r = 0; r < R; ++r) load_stream_v<4>(grads[r] + e0, raw[r]);
+                for (int r = 0; r < R; ++r) load_stream_v<4>(grads[r] + e0, raw[r]);
+            }
+            pv = load_nt4(P + e0);
+            mv = load_nt4(M + e0);
+            vv = load_nt4(V + e0);
         }
-        float4 pv = load_nt4(P + e0);
-        float4 mv = load_nt4(M + e0);
-        float4 vv = load_nt4(V + e0);
-        const Consts k = load_consts(a);
-        float g[kUpdVec];
-        if constexpr (CACHED) {
-            g[0] = gb.x; g[1] = gb.y; g[2] = gb.z; g[3] = gb.w;
-        } else {
-            mean4<R>(raw, grads, e0, g);
-        }
-        float *pf = &pv.x, *mf = &mv.x, *vf = &vv.x;
+        k = load_consts<FOLD>(a);
+        if (has) {
+            float g[kUpdVec];
+            if constexpr (CACHED) {
+                g[0] = gb.x; g[1] = gb.y; g[2] = gb.z; g[3] = gb.w;
+            } else {
+                mean4<R>(raw, grads, e0, g);
+            }
+            float *pf = &pv.x, *mf = &mv.x, *vf = &vv.x;
 #pragma unroll
-        for (int e = 0; e < kUpdVec; ++e) adamw(pf[e], mf[e], vf[e], g[e], k);
-        // a non-finite norm is acted on here and not before the loads, which
-        // would then wait for the norm state: the results pass through an
-        // empty statement, so that the compiler cannot move the branch up
-        int skip = k.nonfinite;
-        asm volatile("" : "+s"(skip) : "v"(pv.x), "v"(pv.y), "v"(pv.z), "v"(pv.w), "v"(mv.x), "v"(mv.y), "v"(mv.z),
-                     "v"(mv.w), "v"(vv.x), "v"(vv.y), "v"(vv.z), "v"(vv.w));
-        if (skip) return;
-        store_nt4(P + e0, pv);
-        store_nt4(M + e0, mv);
-        store_nt4(V + e0, vv);
-        store_nt2(PB + e0, pack_bf16(pf[0], pf[1]), pack_bf16(pf[2], pf[3]));
+            for (int e = 0; e < kUpdVec; ++e) adamw(pf[e], mf[e], vf[e], g[e], k);
+            // a non-finite norm is acted on here and not before the loads,
+            // which would then wait for the norm state: the results pass
+            // through an empty statement, so that the compiler cannot move
+            // the branch up
+            int skip = k.nonfinite;
+            asm volatile("" : "+s"(skip) : "v"(pv.x), "v"(pv.y), "v"(pv.z), "v"(pv.w), "v"(mv.x), "v"(mv.y),
+                         "v"(mv.z), "v"(mv.w), "v"(vv.x), "v"(vv.y), "v"(vv.z), "v"(vv.w));
+            if (!skip) {
+                store_nt4(P + e0, pv);
+                store_nt4(M + e0, mv);
+                store_nt4(V + e0, vv);
+                store_nt2(PB + e0, pack_bf16(pf[0], pf[1]), pack_bf16(pf[2], pf[3]));
+            }
+        }
+        if (stride >= groups - w) break;
+        w += stride;
     }
-    if (q0 == 0 && groups * kUpdVec < n) {
-        const Consts k = load_consts(a);
-        if (k.nonfinite) return;
+    if (w0 == 0 && lane == 0 && !k.nonfinite) {
         for (int64_t i = groups * kUpdVec; i < n; ++i) {
             float gb;
             if constexpr (CACHED) gb = GB[i];
@@ -831,17 +864,17 @@ __device__ __forceinline__ void update_groups(float *__restrict__ P, float *__re
 
 template <int R, bool CACHED>
 __global__ __launch_bounds__(kUpdateThreads) void k_update(UpdateArgs a) {
-    update_groups<R, CACHED>(a.p, a.m, a.v, a.pb, a.g, a.gbar, a.n, (int64_t)blockIdx.x * kUpdateThreads + threadIdx.x,
+    update_groups<R, CACHED, false>(a.p, a.m, a.v, a.pb, a.g, a.gbar, a.n, (int64_t)blockIdx.x * kUpdateThreads,
                              a.stride, a);
 }
 
 // The update of several segments: block b handles the 64 groups from
 // 64 * (b - first) of its segment.
-template <int R, bool CACHED>
+template <int R, bool CACHED, bool FOLD>
 __global__ __launch_bounds__(kUpdateThreads) void k_update_segments(SegTable<R> t, UpdateConsts c) {
     const SegEntry<R> &e = segment_of<R>(t, blockIdx.x);
-    const int64_t q0 = (blockIdx.x - e.first) * kUpdateThreads + threadIdx.x;
-    update_groups<R, CACHED>(e.p, e.m, e.v, e.pb, e.g, e.gbar, e.n, q0, (int64_t)1 << 62, c);
+    update_groups<R, CACHED, FOLD>(e.p, e.m, e.v, e.pb, e.g, e.gbar, e.n, (blockIdx.x - e.first) * kUpdateThreads,
+                             (int64_t)1 << 62, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -1079,7 +1112,8 @@ int fill_table(SegTable<R> &t, const Segment *segs, int n, bool cached_only, F b
 }
 
 template <int R>
-hipError_t norm_segments_r(const Segment *segs, int n, double *partials, int store_lds_pad, hipStream_t s) {
+hipError_t norm_segments_r(const Segment *segs, int n, double *partials, NormState *ns, int store_lds_pad,
+                           hipStream_t s) {
     const bool store = segs[0].gbar != nullptr;
     const int ppt = norm_pairs_per_tile(R, store);
     for (int k = 0; k < n;) {
@@ -1089,6 +1123,7 @@ hipError_t norm_segments_r(const Segment *segs, int n, double *partials, int sto
             a.n = segs[k].n;
             a.partials = partials;
             a.gbar_out = segs[k].gbar;
+            a.ns = ns;
             return norm_r<R>(a, store_lds_pad, s);
         }
         SegTable<R> t{};
@@ -1096,10 +1131,10 @@ hipError_t norm_segments_r(const Segment *segs, int n, double *partials, int sto
         const int done = fill_table<R>(t, segs + k, n - k, false, [&](int64_t e) { return cdiv(e, kTile) * ppt; }, &blocks);
         if (store)
             hipLaunchKernelGGL((k_norm_segments<R, true>), dim3((uint32_t)blocks), dim3(NormShape<R, true>::kThreads),
-                               store_lds_pad, s, t, partials);
+                               store_lds_pad, s, t, partials, ns);
         else
             hipLaunchKernelGGL((k_norm_segments<R, false>), dim3((uint32_t)blocks), dim3(NormShape<R, false>::kThreads),
-                               0, s, t, partials);
+                               0, s, t, partials, ns);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         partials += 2 * blocks;
@@ -1113,7 +1148,7 @@ template <int R, bool CACHED>
 hipError_t update_segments_r(const Segment *segs, int n, const UpdateConsts &c, int lds_pad, int segments_lds_pad,
                              hipStream_t s) {
     for (int k = 0; k < n;) {
-        if (n - k == 1) {
+        if (n - k == 1 && c.sum.n_pairs == 0) {
             UpdateArgs a{};
             static_cast<UpdateConsts &>(a) = c;
             a.p = segs[k].p;
@@ -1129,8 +1164,12 @@ hipError_t update_segments_r(const Segment *segs, int n, const UpdateConsts &c, 
         SegTable<R> t{};
         int64_t blocks = 0;
         const int done = fill_table<R>(t, segs + k, n - k, CACHED, update_blocks, &blocks);
-        hipLaunchKernelGGL((k_update_segments<R, CACHED>), dim3((uint32_t)blocks), dim3(kUpdateThreads),
-                           segments_lds_pad, s, t, c);
+        if (c.sum.n_pairs > 0)
+            hipLaunchKernelGGL((k_update_segments<R, CACHED, true>), dim3((uint32_t)blocks), dim3(kUpdateThreads), 0, s,
+                               t, c);
+        else
+            hipLaunchKernelGGL((k_update_segments<R, CACHED, false>), dim3((uint32_t)blocks), dim3(kUpdateThreads),
+                               segments_lds_pad, s, t, c);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         k += done;
@@ -1176,9 +1215,10 @@ hipError_t launch_norm_partials(int R, const NormArgs &a, int store_lds_pad, hip
     }
 }
 
-hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, int store_lds_pad, hipStream_t s) {
+hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, NormState *ns, int store_lds_pad,
+                                hipStream_t s) {
     switch (R) {
-#define CASE(r) case r: return norm_segments_r<r>(segs, n, partials, store_lds_pad, s);
+#define CASE(r) case r: return norm_segments_r<r>(segs, n, partials, ns, store_lds_pad, s);
         SDP_FOR_EACH_R(CASE)
 #undef CASE
         default: return hipErrorInvalidValue;
@@ -1196,20 +1236,12 @@ hipError_t launch_update_segments(int R, const Segment *segs, int n, const Updat
     }
 }
 
-hipError_t launch_norm_finalize(const double *partials, int64_t n_partials, double *merged, double max_grad_norm,
-                                NormState *ns, hipStream_t s) {
-    if (n_partials > kMergeRun) {
-        if (!merged) return hipErrorInvalidValue;
-        const int64_t blocks = cdiv(n_partials, kMergeRun);
-        hipLaunchKernelGGL(k_norm_merge, dim3((uint32_t)blocks), dim3(kMergeThreads), 0, s, partials, n_partials,
-                           merged);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        partials = merged;
-        n_partials = blocks;
-    }
-    hipLaunchKernelGGL(k_norm_finalize, dim3(1), dim3(kFinalizeThreads), 0, s, partials, n_partials,
-                       max_grad_norm, ns);
+hipError_t launch_norm_finalize(const NormSum &sum, double *merged, hipStream_t s) {
+    if (sum.n_pairs < 1) return hipErrorInvalidValue;
+    const int64_t run = cdiv(cdiv(sum.n_pairs, kMergeRun), kMaxMergeBlocks) * kMergeRun;
+    const int64_t blocks = cdiv(sum.n_pairs, run);
+    if (blocks > 1 && !merged) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_norm_finalize, dim3((uint32_t)blocks), dim3(kFinalizeThreads), 0, s, sum, run, merged);
     return hipGetLastError();
 }
 

@@ -44,7 +44,7 @@ using sdprt::fail;
 
 constexpr int64_t kMaxTiles = SDP_NOALLOC_MAX_TILES;
 constexpr int64_t kMaxPairs = kMaxTiles * sdp::norm_pairs_per_tile(SDP_MAX_RANKS, false);
-constexpr int64_t kMaxMerged = (kMaxPairs + sdp::kMergeRun - 1) / sdp::kMergeRun;
+constexpr int64_t kMaxMerged = sdp::kMaxMergeBlocks;
 constexpr size_t kPairBytes = 2 * sizeof(double);
 constexpr size_t kNormStateOffset = (size_t)(kMaxPairs + kMaxMerged) * kPairBytes;
 constexpr size_t kScratchBytes = kNormStateOffset + 256;
@@ -220,14 +220,17 @@ int sdp_agg_adam_step_noalloc(const sdp_segment *segs, int32_t n_segs, const sdp
     for (int32_t s = 0; s < n_segs; ++s)
         ks[s] = {segs[s].master, segs[s].exp_avg, segs[s].exp_avg_sq, segs[s].param_bf16, segs[s].grads, nullptr,
                  segs[s].numel};
-    NA_HIP(sdp::launch_norm_segments(R, ks, n_segs, partials, 0, st));
-    const int64_t ppt = sdp::norm_pairs_per_tile(R, false);  // at most kMaxPairs / kMaxTiles
-    NA_HIP(sdp::launch_norm_finalize(partials, tiles * ppt, merged, hp->max_grad_norm, ns, st));
+    NA_HIP(sdp::launch_norm_segments(R, ks, n_segs, partials, ns, 0, st));
+    // at most kMaxPairs pairs; few of them the update sums itself
+    const sdp::NormSum sum = {partials, tiles * sdp::norm_pairs_per_tile(R, false), hp->max_grad_norm, ns, nullptr};
+    const bool folds = sum.n_pairs <= sdp::kFoldPairs;
+    if (!folds) NA_HIP(sdp::launch_norm_finalize(sum, merged, st));
     // the fused update, reading the clip coefficient from the norm state,
     // with the per-step constants computed as for every other mode
     sdp::UpdateConsts c{};
     c.ns = ns;
     sdprt::fill_consts(hp, c);
+    if (folds) c.sum = sum;
     NA_HIP(sdp::launch_update_segments(R, ks, n_segs, c, dev.update_lds_pad, dev.update_segments_lds_pad, st));
     if (grad_norm_out) {
         sdp::NormState hs{};

@@ -260,6 +260,7 @@ struct sdp_ctx {
     int64_t gbar_cap = 0;
     sdp::NormState *ns = nullptr;       // device
     sdp::NormState *ns_host = nullptr;  // pinned mirror for read-back
+    sdp::NormState *ns_mirror = nullptr;  // its device mapping
     int update_max_blocks = 0;     // 0: one 8-element group per lane
     int update_lds_pad = 0;        // dynamic LDS bytes per update block (residency cap); 0: no cap
     int update_segments_lds_pad = 0;  // the same for the update of several segments
@@ -327,7 +328,7 @@ int order_after_last(sdp_ctx *ctx, hipStream_t s);
 int mark_done(sdp_ctx *ctx, hipStream_t s);
 int read_norm(sdp_ctx *ctx, hipStream_t s, NormState *out);
 int device_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool store_gbar,
-                double max_grad_norm, hipStream_t s);
+                double max_grad_norm, bool folds, hipStream_t s);
 int sync_streams(sdp_ctx *ctx);
 
 // SDP_FLAG_DEBUG_JITTER: a random delay of 0-200 us enqueued on stream s

@@ -6,8 +6,8 @@
 // step-time model in sdp_schedule.cpp.
 //
 // Device mode (sdp_agg_adam_step): per call, one norm-partials launch, the
-// finalize (one launch, or two above 2,048 span partials) and one fused-update
-// launch, all on the caller's stream (for more segments than a launch takes,
+// finalize (for up to 256 span partials part of the update) and one
+// fused-update launch, all on the caller's stream (for more segments than a launch takes,
 // 19 to 32 by the number of ranks, one for each so many).  The clip
 // coefficient stays in device memory.
 #include "sdp_rt.h"
@@ -203,9 +203,8 @@ int ensure_partials(sdp_ctx *ctx, int64_t pairs) {
     if (ctx->partials) HIP_TRY(hipFree(ctx->partials));
     ctx->partials = nullptr;
     ctx->partials_cap = 0;
-    // each span partial is a double-double pair; the finalize's first stage
-    // writes one pair per kMergeRun of them after the last
-    const int64_t room = pairs + cdiv(pairs, sdp::kMergeRun);
+    // each span partial is a pair; the finalize's blocks write one each after the last
+    const int64_t room = pairs + sdp::kMaxMergeBlocks;
     if (hipMalloc(&ctx->partials, (size_t)room * 2 * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
         ctx->partials = nullptr;
@@ -312,16 +311,20 @@ int norm_launch(sdp_ctx *ctx, int32_t R, const uint16_t *const *g, int64_t n, do
     a.n = n;
     a.partials = partials;
     a.gbar_out = gbar_out;
+    a.ns = ctx->ns;
     hipEvent_t t0 = timed_begin(ctx, s);
     HIP_TRY(sdp::launch_norm_partials(R, a, norm_store_lds_pad(ctx, R), s));
     timed_end(ctx, s, t0, kNorm, n);
     return SDP_OK;
 }
 
+sdp::NormSum norm_sum(const sdp_ctx *ctx, int64_t pairs, double max_grad_norm) {
+    return {ctx->partials, pairs, max_grad_norm, ctx->ns, ctx->ns_mirror};
+}
+
 int finalize_launch(sdp_ctx *ctx, int64_t pairs, double max_grad_norm, hipStream_t s) {
     hipEvent_t t0 = timed_begin(ctx, s);
-    HIP_TRY(sdp::launch_norm_finalize(ctx->partials, pairs, ctx->partials + 2 * ctx->partials_cap, max_grad_norm,
-                                      ctx->ns, s));
+    HIP_TRY(sdp::launch_norm_finalize(norm_sum(ctx, pairs, max_grad_norm), ctx->partials + 2 * ctx->partials_cap, s));
     timed_end(ctx, s, t0, kFinalize, pairs);
     return SDP_OK;
 }
@@ -398,7 +401,7 @@ void jitter_host(sdp_ctx *ctx) {
 }
 
 int read_norm(sdp_ctx *ctx, hipStream_t s, NormState *out) {
-    HIP_TRY(hipMemcpyAsync(ctx->ns_host, ctx->ns, sizeof(NormState), hipMemcpyDeviceToHost, s));
+    // the kernel that made the norm state wrote it to pinned memory too
     HIP_TRY(hipStreamSynchronize(s));
     *out = *ctx->ns_host;
     return SDP_OK;
@@ -433,17 +436,19 @@ int64_t total_elems(const sdp_segment *segs, int32_t n_segs) {
 }  // namespace
 
 int device_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool store_gbar,
-                double max_grad_norm, hipStream_t s) {
+                double max_grad_norm, bool folds, hipStream_t s) {
     const int ppt = sdp::norm_pairs_per_tile(R, store_gbar);
     const std::vector<sdp::Segment> ks = kernel_segments(ctx, segs, n_segs, plan, store_gbar);
     hipEvent_t t0 = timed_begin(ctx, s);
-    HIP_TRY(sdp::launch_norm_segments(R, ks.data(), n_segs, ctx->partials, norm_store_lds_pad(ctx, R), s));
+    HIP_TRY(sdp::launch_norm_segments(R, ks.data(), n_segs, ctx->partials, ctx->ns, norm_store_lds_pad(ctx, R), s));
     timed_end(ctx, s, t0, kNorm, total_elems(segs, n_segs));
+    if (folds) return SDP_OK;
     return finalize_launch(ctx, plan.tiles * ppt, max_grad_norm, s);
 }
 
+// folds: the update sums the span pairs itself (there was no finalize).
 int device_update(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool stored_gbar,
-                  const sdp_adamw_params *hp, hipStream_t s) {
+                  const sdp_adamw_params *hp, bool folds, hipStream_t s) {
     // a cap on the blocks of a launch: one launch per segment
     if (ctx->update_max_blocks > 0) {
         for (int32_t k = 0; k < n_segs; ++k) {
@@ -457,6 +462,7 @@ int device_update(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t
     sdp::UpdateConsts c{};
     c.ns = ctx->ns;
     fill_consts(hp, c);
+    if (folds) c.sum = norm_sum(ctx, plan.tiles * sdp::norm_pairs_per_tile(R, stored_gbar), hp->max_grad_norm);
     hipEvent_t t0 = timed_begin(ctx, s);
     HIP_TRY(sdp::launch_update_segments(R, ks.data(), n_segs, c, ctx->update_lds_pad, ctx->update_segments_lds_pad, s));
     timed_end(ctx, s, t0, kUpdate, total_elems(segs, n_segs));
@@ -814,6 +820,12 @@ int sdp_ctx_create(sdp_ctx **out, int device, int64_t max_chunk_elems, int32_t m
         (void)hipGetLastError();
         return bail(fail(SDP_ERR_OUT_OF_MEMORY, "cannot allocate the pinned norm mirror"));
     }
+    {
+        ptrdiff_t map = 0;
+        rc = device_map_offset(c->ns_host, &map);
+        if (rc != SDP_OK) return bail(rc);
+        c->ns_mirror = (NormState *)((char *)c->ns_host + map);
+    }
     // pinned streamed mode with the BF16 parameters rounded on the host waits
     // on each chunk's returning copies, and then the runtime's large copies
     // ran slower than the library's kernel (183 against 144 ms per step on
@@ -913,8 +925,12 @@ int sdp_agg_adam_step(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, con
     if (store) SDP_TRY(ensure_gbar(ctx, plan.gbar_elems));
     hipStream_t s = (hipStream_t)stream;
     SDP_TRY(order_after_last(ctx, s));
-    SDP_TRY(device_norm(ctx, segs, n_segs, R, plan, store, hp->max_grad_norm, s));
-    SDP_TRY(device_update(ctx, segs, n_segs, R, plan, store, hp, s));
+    // few pairs: the update sums them (with per-launch timing on, or a cap on
+    // a launch's blocks, the finalize stays a launch of its own)
+    const bool folds = plan.tiles * sdp::norm_pairs_per_tile(R, store) <= sdp::kFoldPairs && !ctx->timing &&
+                       ctx->update_max_blocks == 0;
+    SDP_TRY(device_norm(ctx, segs, n_segs, R, plan, store, hp->max_grad_norm, folds, s));
+    SDP_TRY(device_update(ctx, segs, n_segs, R, plan, store, hp, folds, s));
     SDP_TRY(mark_done(ctx, s));
     if (grad_norm_out) {
         NormState st;
@@ -938,7 +954,7 @@ int sdp_grad_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int dev
         SDP_TRY(ensure_partials(ctx, p.tiles * sdp::norm_pairs_per_tile(R, false)));
         hipStream_t s = (hipStream_t)stream;
         SDP_TRY(order_after_last(ctx, s));
-        SDP_TRY(device_norm(ctx, segs, n_segs, R, p, false, 0.0, s));
+        SDP_TRY(device_norm(ctx, segs, n_segs, R, p, false, 0.0, false, s));
         SDP_TRY(mark_done(ctx, s));
         SDP_TRY(read_norm(ctx, s, &st));
     } else {
@@ -1112,6 +1128,7 @@ int sdp_probe_norm_pattern(sdp_ctx *ctx, const sdp_segment *seg, void *stream) {
     a.n = seg->numel;
     a.partials = ctx->partials;
     a.gbar_out = ctx->gbar;
+    a.ns = ctx->ns;
     HIP_TRY(sdp::launch_norm_pattern(R, a, norm_store_lds_pad(ctx, R), s));
     SDP_TRY(mark_done(ctx, s));
     return SDP_OK;

@@ -78,3 +78,31 @@ def test_many_segments(sdp, R, count):
             check_state(dev.host(), ref)
     finally:
         sdp.sdp_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("R,n", [(2, 16 * 65536), (2, 16 * 65536 + 1), (3, 128 * 65536), (3, 128 * 65536 + 1),
+                                 (8, 65536), (8, 65537), (8, 8 * 65536 + 1), (16, 70 * 65536), (1, 33 * 65536 - 3)])
+def test_pair_counts_at_the_finalizes_edges(sdp, R, n):
+    """256 pairs are summed by the update itself, up to 2,048 by one block of
+    the finalize, more by several; three steps, so that the count of blocks is
+    used again, and without reading the norm back in between."""
+    log(f"finalize edges R={R} n={n}")
+    masters, grads = rand_inputs([n], R, 1, seed=n % 1000 + R)
+    ref = oracle.State(masters)
+    s = torch.cuda.current_stream()
+    ctx = sdp.sdp_ctx_create(0, 0, R, 0)
+    try:
+        dev, dev2 = DevState(masters, R), DevState(masters, R)
+        dev.set_grads(grads[0])
+        dev2.set_grads(grads[0])
+        for t in (1, 2, 3):
+            hs, ho = hp_pair(sdp, lr=1e-3, weight_decay=0.02, max_grad_norm=0.05, step=t)
+            _, onorm = oracle.step(ref, grads[0], ho)
+            norm = sdp.sdp_agg_adam_step(ctx, dev.segments(sdp), hs, 0, s, want_norm=t == 3)
+            sdp.sdp_agg_adam_step_noalloc(dev2.segments(sdp), hs, s)
+        assert norm == onorm
+        assert sdp.sdp_ctx_last_norm(ctx)[0] == onorm
+        check_state(dev.host(), ref)
+        check_state(dev2.host(), ref)
+    finally:
+        sdp.sdp_ctx_destroy(ctx)

@@ -245,14 +245,21 @@ SDP_API int sdp_agg_adam_step_noalloc(const sdp_segment *segs, int32_t n_segs, c
                                       void *stream, double *grad_norm_out);
 
 /* Streamed mode: the same update with the states in host memory, as the
- * paper keeps them, moved through the GPU in chunks whose transfers overlap
- * the previous chunk's work, a staging buffer being refilled only after its
- * previous consumer has finished (Design, cross-rank pipelining and chunked
- * overlap within a layer; completion and buffer reuse).  All state and
+ * paper keeps them (Design, shared host state and communication routes).  All state and
  * gradient buffers are pinned host memory
  * (e.g. from sdp_host_alloc), or any host memory when the context was
  * created with SDP_FLAG_STREAM_STAGED.  chunk_elems: a multiple of SDP_NORM_TILE,
  * at most the context's max_chunk_elems, and n_ranks <= its max_ranks.
+ * Pinned memory that the device has mapped (sdp_host_alloc's, hipHostMalloc's)
+ * is used where it is: the kernels read and write it over the link, with no
+ * copies, and hold compute units while they wait for it.  Otherwise -- staged,
+ * with SDP_FLAG_STREAM_HOST_CAST, with a debug flag, with no mapping, or with
+ * the environment variable SDP_STREAM_DIRECT set to 0 or one of the copies'
+ * own set, as read at context creation -- the chunks are copied through the
+ * GPU, their transfers overlapping the previous chunk's work, a staging buffer
+ * being refilled only after its previous consumer has finished (Design,
+ * cross-rank pipelining and chunked overlap within a layer; completion and
+ * buffer reuse):
  * Phase 1 copies each chunk's R gradients host-to-device on the copy
  * stream and runs the norm pass on the compute stream, alternating two
  * staging slots ordered by events; then the norm is finalized and read back.
@@ -425,7 +432,7 @@ typedef struct {
 } sdp_prediction;
 
 /* Schedules the model covers. */
-#define SDP_SCHED_STREAMED 0        /* sdp_stream_step, pinned host states */
+#define SDP_SCHED_STREAMED 0        /* sdp_stream_step, pinned host states, by copies */
 #define SDP_SCHED_STREAMED_STAGED 1 /* sdp_stream_step with SDP_FLAG_STREAM_STAGED */
 #define SDP_SCHED_HOST_ROUTE_F32 2  /* sdp_host_update_step, SDP_GBAR_F32 */
 #define SDP_SCHED_HOST_ROUTE_BF16 3 /* sdp_host_update_step, SDP_GBAR_BF16 */

@@ -251,6 +251,7 @@ struct sdp_ctx {
     // lands with outgoing copies `bo`, run once they have landed
     std::vector<sdprt::Job> pending_cast[sdprt::kOutBufs];
     sdprt::HostPool *copier = nullptr;
+    bool stream_direct = false;    // streamed mode: kernels work on pinned host memory itself where it is mapped
     int staged_copy_threads = 0;   // staged update pass: host copy threads while the DMA runs
     int64_t d2h_kernel_max = 0;    // device-to-host copies up to this many bytes run as k_copy_batch
     int d2h_kernel_blocks = 0;     // blocks per copy of such a launch (0: kD2HLaunchBlocks spread over the copies)
@@ -320,15 +321,15 @@ int residency_pad(const sdp_ctx *ctx, int per_cu, int static_lds);
 int norm_store_lds_pad(const sdp_ctx *ctx, int32_t R);
 int norm_launch(sdp_ctx *ctx, int32_t R, const uint16_t *const *g, int64_t n, double *partials, float *gbar_out,
                 hipStream_t s);
-int finalize_launch(sdp_ctx *ctx, int64_t pairs, double max_grad_norm, hipStream_t s);
+int finalize_launch(sdp_ctx *ctx, int64_t pairs, double max_grad_norm, bool to_host, hipStream_t s);
 void fill_consts(const sdp_adamw_params *hp, sdp::UpdateConsts &a);
 int update_launch(sdp_ctx *ctx, int32_t R, const sdp_adamw_params *hp, float *p, float *m, float *v, uint16_t *pb,
-                  const uint16_t *const *g, const float *gbar, int64_t n, hipStream_t s);
+                  const uint16_t *const *g, const float *gbar, int64_t n, hipStream_t s, int max_blocks, int lds_pad);
 int order_after_last(sdp_ctx *ctx, hipStream_t s);
 int mark_done(sdp_ctx *ctx, hipStream_t s);
 int read_norm(sdp_ctx *ctx, hipStream_t s, NormState *out);
 int device_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool store_gbar,
-                double max_grad_norm, bool folds, hipStream_t s);
+                double max_grad_norm, bool folds, bool to_host, hipStream_t s);
 int sync_streams(sdp_ctx *ctx);
 
 // SDP_FLAG_DEBUG_JITTER: a random delay of 0-200 us enqueued on stream s
@@ -355,6 +356,18 @@ inline bool host_cast(const sdp_ctx *ctx) { return (ctx->flags & SDP_FLAG_STREAM
 size_t off_in_slot(const sdp_ctx *ctx, int sl, const void *p);
 int stream_common_checks(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int64_t chunk, bool grads_only,
                          int32_t *R);
+// Streamed mode's direct path: one-wave blocks of the update (three loads of 16
+// bytes per lane: 393 KB on their way over the link).  ms per
+// step of the Qwen3-8B layer at 16 / 32 / 48 / 64 / 96 / 128 / 192 / 512
+// blocks: 120.7 / 80.6 / 80.0 / 83.8 / 80.1 / 79.8 / 80.7 / 83.2; more of them
+// only disturb the other direction.
+constexpr int kDirectBlocks = 128;
+struct MappedSegments {
+    std::vector<sdp_segment> segs;
+    std::vector<const uint16_t *> grads;
+};
+bool map_segments(const sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, bool grads_only,
+                  MappedSegments *m);
 int stream_norm_phase(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan,
                       const std::vector<Chunk> &chunks, bool store_gbar, double max_grad_norm, bool used[2]);
 

@@ -318,13 +318,14 @@ int norm_launch(sdp_ctx *ctx, int32_t R, const uint16_t *const *g, int64_t n, do
     return SDP_OK;
 }
 
-sdp::NormSum norm_sum(const sdp_ctx *ctx, int64_t pairs, double max_grad_norm) {
-    return {ctx->partials, pairs, max_grad_norm, ctx->ns, ctx->ns_mirror};
+// to_host: the norm state goes to the pinned mirror too, for read_norm.
+sdp::NormSum norm_sum(const sdp_ctx *ctx, int64_t pairs, double max_grad_norm, bool to_host) {
+    return {ctx->partials, pairs, max_grad_norm, ctx->ns, to_host ? ctx->ns_mirror : nullptr};
 }
 
-int finalize_launch(sdp_ctx *ctx, int64_t pairs, double max_grad_norm, hipStream_t s) {
+int finalize_launch(sdp_ctx *ctx, int64_t pairs, double max_grad_norm, bool to_host, hipStream_t s) {
     hipEvent_t t0 = timed_begin(ctx, s);
-    HIP_TRY(sdp::launch_norm_finalize(norm_sum(ctx, pairs, max_grad_norm), ctx->partials + 2 * ctx->partials_cap, s));
+    HIP_TRY(sdp::launch_norm_finalize(norm_sum(ctx, pairs, max_grad_norm, to_host), ctx->partials + 2 * ctx->partials_cap, s));
     timed_end(ctx, s, t0, kFinalize, pairs);
     return SDP_OK;
 }
@@ -344,7 +345,7 @@ void fill_consts(const sdp_adamw_params *hp, sdp::UpdateConsts &a) {
 }
 
 int update_launch(sdp_ctx *ctx, int32_t R, const sdp_adamw_params *hp, float *p, float *m, float *v, uint16_t *pb,
-                  const uint16_t *const *g, const float *gbar, int64_t n, hipStream_t s) {
+                  const uint16_t *const *g, const float *gbar, int64_t n, hipStream_t s, int max_blocks, int lds_pad) {
     sdp::UpdateArgs a{};
     a.p = p;
     a.m = m;
@@ -357,7 +358,7 @@ int update_launch(sdp_ctx *ctx, int32_t R, const sdp_adamw_params *hp, float *p,
     a.ns = ctx->ns;
     fill_consts(hp, a);
     hipEvent_t t0 = timed_begin(ctx, s);
-    HIP_TRY(sdp::launch_update(R, a, ctx->update_max_blocks, ctx->update_lds_pad, s));
+    HIP_TRY(sdp::launch_update(R, a, max_blocks, lds_pad, s));
     timed_end(ctx, s, t0, kUpdate, n);
     return SDP_OK;
 }
@@ -436,25 +437,26 @@ int64_t total_elems(const sdp_segment *segs, int32_t n_segs) {
 }  // namespace
 
 int device_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool store_gbar,
-                double max_grad_norm, bool folds, hipStream_t s) {
+                double max_grad_norm, bool folds, bool to_host, hipStream_t s) {
     const int ppt = sdp::norm_pairs_per_tile(R, store_gbar);
     const std::vector<sdp::Segment> ks = kernel_segments(ctx, segs, n_segs, plan, store_gbar);
     hipEvent_t t0 = timed_begin(ctx, s);
     HIP_TRY(sdp::launch_norm_segments(R, ks.data(), n_segs, ctx->partials, ctx->ns, norm_store_lds_pad(ctx, R), s));
     timed_end(ctx, s, t0, kNorm, total_elems(segs, n_segs));
     if (folds) return SDP_OK;
-    return finalize_launch(ctx, plan.tiles * ppt, max_grad_norm, s);
+    return finalize_launch(ctx, plan.tiles * ppt, max_grad_norm, to_host, s);
 }
 
 // folds: the update sums the span pairs itself (there was no finalize).
 int device_update(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool stored_gbar,
-                  const sdp_adamw_params *hp, bool folds, hipStream_t s) {
+                  const sdp_adamw_params *hp, bool folds, bool to_host, hipStream_t s) {
     // a cap on the blocks of a launch: one launch per segment
     if (ctx->update_max_blocks > 0) {
         for (int32_t k = 0; k < n_segs; ++k) {
             const sdp_segment &g = segs[k];
             SDP_TRY(update_launch(ctx, R, hp, g.master, g.exp_avg, g.exp_avg_sq, g.param_bf16, g.grads,
-                                  stored_gbar ? ctx->gbar + plan.gbar_base[k] : nullptr, g.numel, s));
+                                  stored_gbar ? ctx->gbar + plan.gbar_base[k] : nullptr, g.numel, s,
+                                  ctx->update_max_blocks, ctx->update_lds_pad));
         }
         return SDP_OK;
     }
@@ -462,7 +464,7 @@ int device_update(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t
     sdp::UpdateConsts c{};
     c.ns = ctx->ns;
     fill_consts(hp, c);
-    if (folds) c.sum = norm_sum(ctx, plan.tiles * sdp::norm_pairs_per_tile(R, stored_gbar), hp->max_grad_norm);
+    if (folds) c.sum = norm_sum(ctx, plan.tiles * sdp::norm_pairs_per_tile(R, stored_gbar), hp->max_grad_norm, to_host);
     hipEvent_t t0 = timed_begin(ctx, s);
     HIP_TRY(sdp::launch_update_segments(R, ks.data(), n_segs, c, ctx->update_lds_pad, ctx->update_segments_lds_pad, s));
     timed_end(ctx, s, t0, kUpdate, total_elems(segs, n_segs));
@@ -837,6 +839,12 @@ int sdp_ctx_create(sdp_ctx **out, int device, int64_t max_chunk_elems, int32_t m
     c->d2h_kernel_blocks = 0;
     if (const char *env = std::getenv("SDP_D2H_KERNEL_BLOCKS"))
         c->d2h_kernel_blocks = std::max(1, std::min(65535, std::atoi(env)));
+    // the debug aids perturb the copies, and the variables above choose among
+    // them: such a context makes copies
+    c->stream_direct = !(flags & (SDP_FLAG_STREAM_STAGED | SDP_FLAG_STREAM_HOST_CAST | SDP_FLAG_DEBUG_POISON |
+                                  SDP_FLAG_DEBUG_JITTER)) &&
+                       !std::getenv("SDP_D2H_KERNEL_MAX_BYTES") && !std::getenv("SDP_D2H_KERNEL_BLOCKS");
+    if (const char *env = std::getenv("SDP_STREAM_DIRECT")) c->stream_direct = c->stream_direct && std::atoi(env) != 0;
     if (max_chunk_elems > 0) {
         c->slot_bytes = (size_t)(14 + 2 * max_ranks) * (size_t)max_chunk_elems;
         if (hipMalloc(&c->staging, 2 * c->slot_bytes) != hipSuccess) {
@@ -929,8 +937,8 @@ int sdp_agg_adam_step(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, con
     // a launch's blocks, the finalize stays a launch of its own)
     const bool folds = plan.tiles * sdp::norm_pairs_per_tile(R, store) <= sdp::kFoldPairs && !ctx->timing &&
                        ctx->update_max_blocks == 0;
-    SDP_TRY(device_norm(ctx, segs, n_segs, R, plan, store, hp->max_grad_norm, folds, s));
-    SDP_TRY(device_update(ctx, segs, n_segs, R, plan, store, hp, folds, s));
+    SDP_TRY(device_norm(ctx, segs, n_segs, R, plan, store, hp->max_grad_norm, folds, grad_norm_out != nullptr, s));
+    SDP_TRY(device_update(ctx, segs, n_segs, R, plan, store, hp, folds, grad_norm_out != nullptr, s));
     SDP_TRY(mark_done(ctx, s));
     if (grad_norm_out) {
         NormState st;
@@ -954,7 +962,7 @@ int sdp_grad_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int dev
         SDP_TRY(ensure_partials(ctx, p.tiles * sdp::norm_pairs_per_tile(R, false)));
         hipStream_t s = (hipStream_t)stream;
         SDP_TRY(order_after_last(ctx, s));
-        SDP_TRY(device_norm(ctx, segs, n_segs, R, p, false, 0.0, false, s));
+        SDP_TRY(device_norm(ctx, segs, n_segs, R, p, false, 0.0, false, true, s));
         SDP_TRY(mark_done(ctx, s));
         SDP_TRY(read_norm(ctx, s, &st));
     } else {
@@ -966,7 +974,10 @@ int sdp_grad_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int dev
         SDP_TRY(order_after_last(ctx, ctx->s_copy));
         SDP_TRY(order_after_last(ctx, ctx->s_comp));
         bool used[2] = {false, false};
-        int rc = stream_norm_phase(ctx, segs, n_segs, R, p, chunks, false, 0.0, used);
+        MappedSegments mapped;
+        int rc = map_segments(ctx, segs, n_segs, R, true, &mapped)
+                     ? device_norm(ctx, mapped.segs.data(), n_segs, R, p, false, 0.0, false, true, ctx->s_comp)
+                     : stream_norm_phase(ctx, segs, n_segs, R, p, chunks, false, 0.0, used);
         if (rc == SDP_OK) rc = read_norm(ctx, ctx->s_comp, &st);
         int rc2 = sync_streams(ctx);
         if (rc != SDP_OK) return rc;

@@ -293,8 +293,8 @@ SDP_API int sdp_stream_step(sdp_ctx *ctx, const sdp_segment *host_segs, int32_t 
  * reads the norm back.  Phase 2 walks each segment in pieces of at most
  * chunk_elems elements; at the call's start the pieces grow from
  * chunk_elems/16 by 6/5 per piece, in whole SDP_NORM_TILEs (no growth when
- * chunk_elems/16 is less than SDP_NORM_TILE): the GPU writes the piece's mean gradient into a device
- * staging slot, the copy stream moves it into a pinned stage buffer, and
+ * chunk_elems/16 is less than SDP_NORM_TILE): the GPU writes the piece's mean
+ * gradient into a pinned stage buffer, over the link, and
  * the context's host threads run AdamW on the previous piece meanwhile
  * (double-buffered).  gbar_format SDP_GBAR_BF16
  * rounds the mean gradient to BF16 before the copy, as the paper returns

@@ -52,13 +52,15 @@ void host_adamw(HostPool *pool, const sdp_host::AdamArgs &a, const sdp_host::Ada
 // The host-update route over validated segments (grads in device memory,
 // states in host memory).  Phase 1: the norm pass over the device gradients
 // and the finalize; the norm state comes back to the host.  Phase 2, piece
-// by piece: the GPU writes g_bar of piece j (FP32 or BF16) into device slot
-// j%2 on the compute stream, the copy stream moves it into pinned host buffer
-// j%2, and the host threads update piece j-1 from the other buffer meanwhile.
+// by piece: the GPU writes g_bar of piece j (FP32 or BF16) into pinned host
+// buffer j%2, over the link, and the host threads update piece j-1 from the
+// other buffer meanwhile.  (A device slot, an event, a copy on another stream
+// and another event between them cost the calling thread, which is one of
+// the host threads, about 30 us per piece.)
 // The pieces grow from C/16 to C over the call's start (route_pieces).
 int host_route(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan,
                const sdp_adamw_params *hp, int64_t C, bool bf16, double *grad_norm_out) {
-    hipStream_t sc = ctx->s_comp, sy = ctx->s_copy;
+    hipStream_t sc = ctx->s_comp;
     SDP_TRY(device_norm(ctx, segs, n_segs, R, plan, false, hp->max_grad_norm, false, true, sc));
     NormState st{};
     SDP_TRY(read_norm(ctx, sc, &st));
@@ -75,31 +77,20 @@ int host_route(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R,
         for (const sdp_sched::RoutePiece &pc : sdp_sched::route_pieces(numels, C))
             chunks.push_back({pc.seg, pc.off, pc.len});
     }
-    const size_t esz = bf16 ? 2 : 4;
-    bool used[2] = {false, false};
     auto issue = [&](size_t j) -> int {
         const Chunk &c = chunks[j];
         const int sl = (int)(j & 1);
-        char *dev = ctx->staging + (size_t)sl * ctx->slot_bytes;
-        char *host = ctx->stage + (size_t)sl * stage_bytes(ctx);
-        // the slot's previous copy to the host has read it
-        if (used[sl]) HIP_TRY(hipStreamWaitEvent(sc, ctx->slot_free[sl], 0));
+        // the host has finished with this buffer's previous piece (j - 2)
         sdp::GbarArgs a{};
         for (int32_t r = 0; r < R; ++r) a.g[r] = segs[c.seg].grads[r] + c.off;
         a.n = c.len;
-        a.out = dev;
+        a.out = ctx->stage + (size_t)sl * stage_bytes(ctx) + ctx->stage_map;
         a.bf16 = bf16 ? 1 : 0;
         SDP_TRY(jitter_stream(ctx, sc));
         hipEvent_t t0 = timed_begin(ctx, sc);
-        HIP_TRY(sdp::launch_gbar_out(R, a, sc));
+        HIP_TRY(sdp::launch_gbar_out(R, a, kGbarBlocks, sc));
         timed_end(ctx, sc, t0, kGbar, c.len);
-        // h2d_done doubles as "g_bar of this slot is written" here
-        HIP_TRY(hipEventRecord(ctx->h2d_done[sl], sc));
-        HIP_TRY(hipStreamWaitEvent(sy, ctx->h2d_done[sl], 0));
-        SDP_TRY(jitter_stream(ctx, sy));
-        SDP_TRY(d2h_copies(ctx, {{host, dev}}, {(size_t)c.len * esz}, sy, &ctx->stage_map));
-        HIP_TRY(hipEventRecord(ctx->slot_free[sl], sy));  // in the host buffer; the slot is free
-        used[sl] = true;
+        HIP_TRY(hipEventRecord(ctx->slot_free[sl], sc));  // g_bar is in the host buffer
         return SDP_OK;
     };
     if (!chunks.empty()) SDP_TRY(issue(0));

@@ -174,7 +174,6 @@ constexpr int norm_store_blocks_per_cu(int R) {
 }
 // Its static LDS per block (the block sum of waves 1..3).
 constexpr int norm_static_lds(int R, bool store) { return store && R > 4 ? 0 : (256 - 64) * 16; }
-constexpr int kVec = 8;     // elements per lane per access (16 B of BF16, 32 B of FP32)
 constexpr int kUpdVec = 4;  // fused update: elements per lane (8 B of BF16, 16 B of FP32)
 
 hipError_t launch_norm_partials(int R, const NormArgs &a, int store_lds_pad, hipStream_t s);
@@ -191,7 +190,8 @@ hipError_t launch_update_segments(int R, const Segment *segs, int n, const Updat
 // merged: room for kMaxMergeBlocks pairs (used when n_pairs > kMergeRun).
 hipError_t launch_norm_finalize(const NormSum &sum, double *merged, hipStream_t s);
 hipError_t launch_update(int R, UpdateArgs a, int max_blocks, int lds_pad, hipStream_t s);
-hipError_t launch_gbar_out(int R, const GbarArgs &a, hipStream_t s);
+// out: pinned host memory as the device sees it.
+hipError_t launch_gbar_out(int R, const GbarArgs &a, int max_blocks, hipStream_t s);
 hipError_t launch_update_pattern(int R, const UpdateArgs &a, int lds_pad, hipStream_t s);
 hipError_t launch_norm_pattern(int R, const NormArgs &a, int store_lds_pad, hipStream_t s);
 hipError_t launch_cast_bf16(const float *src, uint16_t *dst, int64_t n, hipStream_t s);

@@ -61,7 +61,7 @@ void host_adamw(HostPool *pool, const sdp_host::AdamArgs &a, const sdp_host::Ada
 int host_route(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan,
                const sdp_adamw_params *hp, int64_t C, bool bf16, double *grad_norm_out) {
     hipStream_t sc = ctx->s_comp;
-    SDP_TRY(device_norm(ctx, segs, n_segs, R, plan, false, hp->max_grad_norm, false, true, sc));
+    SDP_TRY(device_norm(ctx, segs, n_segs, R, plan, false, hp->max_grad_norm, NormRun(), sc));
     NormState st{};
     SDP_TRY(read_norm(ctx, sc, &st));
     if (grad_norm_out) *grad_norm_out = st.norm;

@@ -42,6 +42,7 @@ struct NormArgs {
     double *partials;
     float *gbar_out;
     NormState *ns;  // its arrival count is cleared
+    int32_t keep;   // see keep_in_cache
 };
 
 // What an update needs beside its segment: the norm state, or the span pairs
@@ -55,6 +56,7 @@ struct UpdateConsts {
     double step_size;  // lr / (1 - beta1^t)
     double inv_bc2;    // 1 / (1 - beta2^t)
     double eps;
+    int32_t keep;  // see keep_in_cache
     NormSum sum;
 };
 
@@ -148,7 +150,7 @@ constexpr int kMergeRun = 2048;
 constexpr int kMaxMergeBlocks = 128;
 // Up to this many pairs every wave of the update sums them itself, behind its
 // loads, which saves the finalize's launch: four pairs per lane.  1M elements,
-// R = 2 (256 pairs): 18.9 us per step with the finalize, 14.6 without.  Beyond
+// R = 2 (256 pairs): 18.9 us per step with the finalize, 16.4 without.  Beyond
 // it the sum would be repeated by too many waves.
 constexpr int kFoldPairs = 256;
 constexpr int kUpdateThreads = 64;
@@ -176,13 +178,32 @@ constexpr int norm_store_blocks_per_cu(int R) {
 constexpr int norm_static_lds(int R, bool store) { return store && R > 4 ? 0 : (256 - 64) * 16; }
 constexpr int kUpdVec = 4;  // fused update: elements per lane (8 B of BF16, 16 B of FP32)
 
+// Which accesses of a device-mode call leave the non-temporal hint out, so that
+// the 256 MB last-level cache may keep their lines until the update comes for
+// them: the norm pass's reads of the gradients or its stores of g_bar, and the
+// update's reads of the same.  Plain reads alone are slower (6.5 against 7.1
+// TB/s), so this pays only while enough is still there.  us per step, hint /
+// norm pass without it / update without it too, by the call's gradient bytes:
+//   R = 4:  64 MB 62.9 / 61.3 / 59.4;  128 MB 115.8 / 110.5 / 110.5;  384 MB
+//           318 / 307 / 331;  768 MB 630 / 630 / 652;  1.6 GB 1316 / 1335 / 1359
+//   R = 2:  64 MB 95.4 / 91.4 / 91.0;  384 MB 516 / 499 / 524;  1.2 GB 1577 / 1580
+//   R = 1:  64 MB 159 / 154 / 153;  384 MB 916 / 898 / 920;  1.2 GB 2807 / 2796
+// and with stored g_bar (R = 8) by its bytes, hint / stores without / reads too:
+//   64 MB 134.7 / 132.7 / 130.5;  96 MB 195.4 / 192.5 / 189.8;  128 MB 254.8 /
+//   251.3 / 255.4;  256 MB 497 / 490 / 495;  512 MB 1003 / 1013 / 1048
+constexpr int kKeepNorm = 1, kKeepUpdate = 2;
+constexpr int keep_in_cache(int R, bool store, int64_t elems) {
+    return store ? (elems <= 75000000 ? kKeepNorm : 0) | (elems <= 25000000 ? kKeepUpdate : 0)
+                 : (elems <= 400000000 / R ? kKeepNorm : 0) | (elems <= 50000000 / R ? kKeepUpdate : 0);
+}
+
 hipError_t launch_norm_partials(int R, const NormArgs &a, int store_lds_pad, hipStream_t s);
 // The norm pass over n segments (all with gbar or none), in as few launches
 // as their arguments allow.  partials: the first pair of the first segment;
 // each segment's pairs (norm_pairs_per_tile per tile) follow the previous
 // one's.
-hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, NormState *ns, int store_lds_pad,
-                                hipStream_t s);
+hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, NormState *ns, int keep,
+                                int store_lds_pad, hipStream_t s);
 // The update of n segments (all from gbar or none), likewise.
 // lds_pad: for one segment, segments_lds_pad: for several.
 hipError_t launch_update_segments(int R, const Segment *segs, int n, const UpdateConsts &c, int lds_pad,

@@ -22,9 +22,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Streaming accesses: every array of the two passes is touched once per pass
-// and is far larger than the 256 MB last-level cache, so the kernels load and
-// store with the non-temporal hint (the cache does not keep the lines).
+// Streaming accesses: every array of the two passes is touched once per pass,
+// so the kernels load and store with the non-temporal hint (the cache does not
+// keep the lines), except where keep_in_cache says otherwise.
 __device__ __forceinline__ float4 load_nt4(const float *p) {
     const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
     return make_float4(t.x, t.y, t.z, t.w);
@@ -409,16 +409,18 @@ __device__ __forceinline__ void block_merge(double &hi, double &lo) {
 // A lane's order, the butterfly and the wave order are fixed, so a span's
 // partial depends on its contents only.
 //
-// Gradients and g_bar move with non-temporal loads and stores: they are not
-// reused within the pass, and the 256 MB last-level cache cannot hold them
-// until the update reads g_bar back.
-template <int V>
+// Gradients and g_bar move with non-temporal loads and stores, except in calls
+// small enough for the last-level cache to keep some of them for the update
+// (keep_in_cache).
+template <int V, bool NT = true>
 __device__ __forceinline__ void load_stream_v(const uint16_t *p, uint32_t (&w)[V / 2]) {
     if constexpr (V == 8) {
-        const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+        const u32x4 *q = reinterpret_cast<const u32x4 *>(p);
+        const u32x4 t = NT ? __builtin_nontemporal_load(q) : *q;
         w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
     } else {
-        const u32x2 t = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(p));
+        const u32x2 *q = reinterpret_cast<const u32x2 *>(p);
+        const u32x2 t = NT ? __builtin_nontemporal_load(q) : *q;
         w[0] = t.x; w[1] = t.y;
     }
 }
@@ -465,7 +467,7 @@ __device__ __forceinline__ uint32_t top_exponent(const float *g) {
 
 // The pair of span `blk` of the n-element segment g, and its g_bar if STORE.
 // Valid in thread 0.
-template <int R, bool STORE, class S>
+template <int R, bool STORE, bool KEEP, class S>
 __device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, int64_t blk, float *gbar, double &hi,
                                           double &lo) {
     constexpr int V = S::kVec, T = S::kThreads, J = S::kBatch;
@@ -486,7 +488,7 @@ __device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, i
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (q < groups) {
-                    load_stream_v<V>(g[r] + span0 + q * V, raw[j][r]);
+                    load_stream_v<V, STORE || !KEEP>(g[r] + span0 + q * V, raw[j][r]);
                 } else {
 #pragma unroll
                     for (int w = 0; w < V / 2; ++w) raw[j][r][w] = 0;
@@ -520,10 +522,13 @@ __device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, i
                     const uint32_t q = (uint32_t)(it * J + j) * T + threadIdx.x;
                     if (q < groups) {
 #pragma unroll
-                        for (int h = 0; h < V / 4; ++h)
-                            store_nt4(gbar + span0 + q * V + 4 * h,
-                                      make_float4(m[j * V + 4 * h], m[j * V + 4 * h + 1], m[j * V + 4 * h + 2],
-                                                  m[j * V + 4 * h + 3]));
+                        for (int h = 0; h < V / 4; ++h) {
+                            float *at = gbar + span0 + q * V + 4 * h;
+                            const float4 x = make_float4(m[j * V + 4 * h], m[j * V + 4 * h + 1], m[j * V + 4 * h + 2],
+                                                         m[j * V + 4 * h + 3]);
+                            if constexpr (KEEP) *reinterpret_cast<float4 *>(at) = x;
+                            else store_nt4(at, x);
+                        }
                     }
                 }
             }
@@ -562,15 +567,27 @@ __device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, i
     block_merge<T>(hi, lo);
 }
 
-template <int R, bool WRITE_GBAR>
-__global__ __launch_bounds__((NormShape<R, WRITE_GBAR>::kThreads)) void k_norm_partials(NormArgs a) {
+template <int R, bool WRITE_GBAR, bool KEEP>
+__device__ __forceinline__ void norm_partials(const NormArgs &a) {
     double hi, lo;
-    norm_span<R, WRITE_GBAR, NormShape<R, WRITE_GBAR>>(a.g, a.n, blockIdx.x, a.gbar_out, hi, lo);
+    norm_span<R, WRITE_GBAR, KEEP, NormShape<R, WRITE_GBAR>>(a.g, a.n, blockIdx.x, a.gbar_out, hi, lo);
     if (threadIdx.x == 0) {
         a.partials[2 * blockIdx.x] = hi;
         a.partials[2 * blockIdx.x + 1] = lo;
         if (blockIdx.x == 0) a.ns->arrived = 0;
     }
+}
+
+// Two kernels, here and in the update, because a branch between a plain and a
+// non-temporal access is merged into one plain access by the compiler.
+template <int R, bool WRITE_GBAR>
+__global__ __launch_bounds__((NormShape<R, WRITE_GBAR>::kThreads)) void k_norm_partials(NormArgs a) {
+    norm_partials<R, WRITE_GBAR, false>(a);
+}
+
+template <int R, bool WRITE_GBAR>
+__global__ __launch_bounds__((NormShape<R, WRITE_GBAR>::kThreads)) void k_norm_partials_keep(NormArgs a) {
+    norm_partials<R, WRITE_GBAR, true>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -615,13 +632,13 @@ __device__ __forceinline__ const SegEntry<R> &segment_of(const SegTable<R> &t, u
     return t.seg[s];
 }
 
-template <int R, bool WRITE_GBAR>
+template <int R, bool WRITE_GBAR, bool KEEP>
 __global__ __launch_bounds__((NormShape<R, WRITE_GBAR>::kThreads)) void k_norm_segments(SegTable<R> t,
                                                                                       double *partials,
                                                                                       NormState *ns) {
     const SegEntry<R> &e = segment_of<R>(t, blockIdx.x);
     double hi, lo;
-    norm_span<R, WRITE_GBAR, NormShape<R, WRITE_GBAR>>(e.g, e.n, blockIdx.x - e.first, e.gbar, hi, lo);
+    norm_span<R, WRITE_GBAR, KEEP, NormShape<R, WRITE_GBAR>>(e.g, e.n, blockIdx.x - e.first, e.gbar, hi, lo);
     if (threadIdx.x == 0) {
         partials[2 * (int64_t)blockIdx.x] = hi;
         partials[2 * (int64_t)blockIdx.x + 1] = lo;
@@ -789,9 +806,9 @@ __device__ __forceinline__ Consts load_consts(const UpdateConsts &a) {
 // w0 + stride + l, ..., and lane 0 of the segment's first wave its ragged tail
 // of fewer than 4 elements.  Each access of the wave is one contiguous run
 // (1 KB of every FP32 array, 512 B of every BF16 one).
-// Every load and store is non-temporal: under the residency cap this
-// measured about 5% faster than plain accesses to the states and g_bar.
-template <int R, bool CACHED, bool FOLD>
+// Every access to the states is non-temporal: under the residency cap this
+// measured about 5% faster than plain accesses.
+template <int R, bool CACHED, bool FOLD, bool KEEP>
 __device__ __forceinline__ void update_groups(float *__restrict__ P, float *__restrict__ M, float *__restrict__ V,
                                               uint16_t *__restrict__ PB, const uint16_t *const *grads,
                                               const float *__restrict__ GB, int64_t n, int64_t w0, int64_t stride,
@@ -806,11 +823,10 @@ __device__ __forceinline__ void update_groups(float *__restrict__ P, float *__re
         uint32_t raw[R][2];
         if (has) {
             if constexpr (CACHED) {
-                gb = load_nt4(GB + e0);
+                gb = KEEP ? *reinterpret_cast<const float4 *>(GB + e0) : load_nt4(GB + e0);
             } else {
-                // read once: non-temporal, as in the norm pass
 #pragma unroll
-                for (int r = 0; r < R; ++r) load_stream_v<4>(grads[r] + e0, raw[r]);
+                for (int r = 0; r < R; ++r) load_stream_v<4, !KEEP>(grads[r] + e0, raw[r]);
             }
             pv = load_nt4(P + e0);
             mv = load_nt4(M + e0);
@@ -859,16 +875,22 @@ __device__ __forceinline__ void update_groups(float *__restrict__ P, float *__re
 
 template <int R, bool CACHED>
 __global__ __launch_bounds__(kUpdateThreads) void k_update(UpdateArgs a) {
-    update_groups<R, CACHED, false>(a.p, a.m, a.v, a.pb, a.g, a.gbar, a.n, (int64_t)blockIdx.x * kUpdateThreads,
-                             a.stride, a);
+    update_groups<R, CACHED, false, false>(a.p, a.m, a.v, a.pb, a.g, a.gbar, a.n,
+                                           (int64_t)blockIdx.x * kUpdateThreads, a.stride, a);
+}
+
+template <int R, bool CACHED>
+__global__ __launch_bounds__(kUpdateThreads) void k_update_keep(UpdateArgs a) {
+    update_groups<R, CACHED, false, true>(a.p, a.m, a.v, a.pb, a.g, a.gbar, a.n,
+                                          (int64_t)blockIdx.x * kUpdateThreads, a.stride, a);
 }
 
 // The update of several segments: block b handles the 64 groups from
 // 64 * (b - first) of its segment.
-template <int R, bool CACHED, bool FOLD>
+template <int R, bool CACHED, bool FOLD, bool KEEP>
 __global__ __launch_bounds__(kUpdateThreads) void k_update_segments(SegTable<R> t, UpdateConsts c) {
     const SegEntry<R> &e = segment_of<R>(t, blockIdx.x);
-    update_groups<R, CACHED, FOLD>(e.p, e.m, e.v, e.pb, e.g, e.gbar, e.n, (blockIdx.x - e.first) * kUpdateThreads,
+    update_groups<R, CACHED, FOLD, KEEP>(e.p, e.m, e.v, e.pb, e.g, e.gbar, e.n, (blockIdx.x - e.first) * kUpdateThreads,
                              (int64_t)1 << 62, c);
 }
 
@@ -1050,8 +1072,11 @@ template <int R, bool STORE>
 hipError_t norm_rs(const NormArgs &a, int lds_pad, hipStream_t s) {
     using S = NormShape<R, STORE>;
     static_assert(kTile / S::kSpan == norm_pairs_per_tile(R, STORE), "the host's pair count");
-    hipLaunchKernelGGL((k_norm_partials<R, STORE>), dim3((uint32_t)(cdiv(a.n, kTile) * (kTile / S::kSpan))),
-                       dim3(S::kThreads), lds_pad, s, a);
+    const dim3 grid((uint32_t)(cdiv(a.n, kTile) * (kTile / S::kSpan))), block(S::kThreads);
+    if (a.keep)
+        hipLaunchKernelGGL((k_norm_partials_keep<R, STORE>), grid, block, lds_pad, s, a);
+    else
+        hipLaunchKernelGGL((k_norm_partials<R, STORE>), grid, block, lds_pad, s, a);
     return hipGetLastError();
 }
 
@@ -1060,13 +1085,19 @@ hipError_t norm_r(const NormArgs &a, int store_lds_pad, hipStream_t s) {
     return a.gbar_out ? norm_rs<R, true>(a, store_lds_pad, s) : norm_rs<R, false>(a, 0, s);
 }
 
+template <int R, bool CACHED>
+hipError_t update_rc(const UpdateArgs &a, int64_t blocks, int lds_pad, hipStream_t s) {
+    const dim3 grid((uint32_t)blocks), block(kUpdateThreads);
+    if (a.keep)
+        hipLaunchKernelGGL((k_update_keep<R, CACHED>), grid, block, lds_pad, s, a);
+    else
+        hipLaunchKernelGGL((k_update<R, CACHED>), grid, block, lds_pad, s, a);
+    return hipGetLastError();
+}
+
 template <int R>
 hipError_t update_r(const UpdateArgs &a, int64_t blocks, int lds_pad, hipStream_t s) {
-    if (a.gbar)
-        hipLaunchKernelGGL((k_update<1, true>), dim3((uint32_t)blocks), dim3(kUpdateThreads), lds_pad, s, a);
-    else
-        hipLaunchKernelGGL((k_update<R, false>), dim3((uint32_t)blocks), dim3(kUpdateThreads), lds_pad, s, a);
-    return hipGetLastError();
+    return a.gbar ? update_rc<1, true>(a, blocks, lds_pad, s) : update_rc<R, false>(a, blocks, lds_pad, s);
 }
 
 // Block counts of one segment in the batched launches.
@@ -1107,7 +1138,7 @@ int fill_table(SegTable<R> &t, const Segment *segs, int n, bool cached_only, F b
 }
 
 template <int R>
-hipError_t norm_segments_r(const Segment *segs, int n, double *partials, NormState *ns, int store_lds_pad,
+hipError_t norm_segments_r(const Segment *segs, int n, double *partials, NormState *ns, int keep, int store_lds_pad,
                            hipStream_t s) {
     const bool store = segs[0].gbar != nullptr;
     const int ppt = norm_pairs_per_tile(R, store);
@@ -1119,17 +1150,17 @@ hipError_t norm_segments_r(const Segment *segs, int n, double *partials, NormSta
             a.partials = partials;
             a.gbar_out = segs[k].gbar;
             a.ns = ns;
+            a.keep = keep;
             return norm_r<R>(a, store_lds_pad, s);
         }
         SegTable<R> t{};
         int64_t blocks = 0;
         const int done = fill_table<R>(t, segs + k, n - k, false, [&](int64_t e) { return cdiv(e, kTile) * ppt; }, &blocks);
-        if (store)
-            hipLaunchKernelGGL((k_norm_segments<R, true>), dim3((uint32_t)blocks), dim3(NormShape<R, true>::kThreads),
-                               store_lds_pad, s, t, partials, ns);
-        else
-            hipLaunchKernelGGL((k_norm_segments<R, false>), dim3((uint32_t)blocks), dim3(NormShape<R, false>::kThreads),
-                               0, s, t, partials, ns);
+        const dim3 grid((uint32_t)blocks), block(store ? NormShape<R, true>::kThreads : NormShape<R, false>::kThreads);
+        const int lds_pad = store ? store_lds_pad : 0;
+        auto kernel = store ? (keep ? k_norm_segments<R, true, true> : k_norm_segments<R, true, false>)
+                            : (keep ? k_norm_segments<R, false, true> : k_norm_segments<R, false, false>);
+        hipLaunchKernelGGL(kernel, grid, block, lds_pad, s, t, partials, ns);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         partials += 2 * blocks;
@@ -1159,12 +1190,12 @@ hipError_t update_segments_r(const Segment *segs, int n, const UpdateConsts &c, 
         SegTable<R> t{};
         int64_t blocks = 0;
         const int done = fill_table<R>(t, segs + k, n - k, CACHED, update_blocks, &blocks);
-        if (c.sum.n_pairs > 0)
-            hipLaunchKernelGGL((k_update_segments<R, CACHED, true>), dim3((uint32_t)blocks), dim3(kUpdateThreads), 0, s,
-                               t, c);
-        else
-            hipLaunchKernelGGL((k_update_segments<R, CACHED, false>), dim3((uint32_t)blocks), dim3(kUpdateThreads),
-                               segments_lds_pad, s, t, c);
+        // a call small enough to fold keeps its lines too
+        const bool fold = c.sum.n_pairs > 0;
+        auto kernel = fold     ? k_update_segments<R, CACHED, true, true>
+                      : c.keep ? k_update_segments<R, CACHED, false, true>
+                               : k_update_segments<R, CACHED, false, false>;
+        hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks), dim3(kUpdateThreads), fold ? 0 : segments_lds_pad, s, t, c);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         k += done;
@@ -1210,10 +1241,10 @@ hipError_t launch_norm_partials(int R, const NormArgs &a, int store_lds_pad, hip
     }
 }
 
-hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, NormState *ns, int store_lds_pad,
-                                hipStream_t s) {
+hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, NormState *ns, int keep,
+                                int store_lds_pad, hipStream_t s) {
     switch (R) {
-#define CASE(r) case r: return norm_segments_r<r>(segs, n, partials, ns, store_lds_pad, s);
+#define CASE(r) case r: return norm_segments_r<r>(segs, n, partials, ns, keep, store_lds_pad, s);
         SDP_FOR_EACH_R(CASE)
 #undef CASE
         default: return hipErrorInvalidValue;

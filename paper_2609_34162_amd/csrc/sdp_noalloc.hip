@@ -220,7 +220,10 @@ int sdp_agg_adam_step_noalloc(const sdp_segment *segs, int32_t n_segs, const sdp
     for (int32_t s = 0; s < n_segs; ++s)
         ks[s] = {segs[s].master, segs[s].exp_avg, segs[s].exp_avg_sq, segs[s].param_bf16, segs[s].grads, nullptr,
                  segs[s].numel};
-    NA_HIP(sdp::launch_norm_segments(R, ks, n_segs, partials, ns, 0, st));
+    int64_t elems = 0;
+    for (int32_t s = 0; s < n_segs; ++s) elems += segs[s].numel;
+    const int keep = sdp::keep_in_cache(R, false, elems);
+    NA_HIP(sdp::launch_norm_segments(R, ks, n_segs, partials, ns, keep & sdp::kKeepNorm, 0, st));
     // at most kMaxPairs pairs; few of them the update sums itself
     const sdp::NormSum sum = {partials, tiles * sdp::norm_pairs_per_tile(R, false), hp->max_grad_norm, ns, nullptr};
     const bool folds = sum.n_pairs <= sdp::kFoldPairs;
@@ -231,6 +234,7 @@ int sdp_agg_adam_step_noalloc(const sdp_segment *segs, int32_t n_segs, const sdp
     c.ns = ns;
     sdprt::fill_consts(hp, c);
     if (folds) c.sum = sum;
+    c.keep = keep & sdp::kKeepUpdate;
     NA_HIP(sdp::launch_update_segments(R, ks, n_segs, c, dev.update_lds_pad, dev.update_segments_lds_pad, st));
     if (grad_norm_out) {
         sdp::NormState hs{};

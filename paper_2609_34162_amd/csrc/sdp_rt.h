@@ -328,8 +328,14 @@ int update_launch(sdp_ctx *ctx, int32_t R, const sdp_adamw_params *hp, float *p,
 int order_after_last(sdp_ctx *ctx, hipStream_t s);
 int mark_done(sdp_ctx *ctx, hipStream_t s);
 int read_norm(sdp_ctx *ctx, hipStream_t s, NormState *out);
+// How a norm pass over device-visible gradients is run.
+struct NormRun {
+    bool folds = false;   // the update sums the span pairs: no finalize
+    bool to_host = true;  // the norm state goes to the pinned mirror too, for read_norm
+    int keep = 0;         // sdp::keep_in_cache
+};
 int device_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool store_gbar,
-                double max_grad_norm, bool folds, bool to_host, hipStream_t s);
+                double max_grad_norm, const NormRun &run, hipStream_t s);
 int sync_streams(sdp_ctx *ctx);
 
 // SDP_FLAG_DEBUG_JITTER: a random delay of 0-200 us enqueued on stream s

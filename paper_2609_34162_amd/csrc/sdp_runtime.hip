@@ -437,19 +437,19 @@ int64_t total_elems(const sdp_segment *segs, int32_t n_segs) {
 }  // namespace
 
 int device_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool store_gbar,
-                double max_grad_norm, bool folds, bool to_host, hipStream_t s) {
+                double max_grad_norm, const NormRun &run, hipStream_t s) {
     const int ppt = sdp::norm_pairs_per_tile(R, store_gbar);
     const std::vector<sdp::Segment> ks = kernel_segments(ctx, segs, n_segs, plan, store_gbar);
     hipEvent_t t0 = timed_begin(ctx, s);
-    HIP_TRY(sdp::launch_norm_segments(R, ks.data(), n_segs, ctx->partials, ctx->ns, norm_store_lds_pad(ctx, R), s));
+    HIP_TRY(sdp::launch_norm_segments(R, ks.data(), n_segs, ctx->partials, ctx->ns, run.keep & sdp::kKeepNorm,
+                                      norm_store_lds_pad(ctx, R), s));
     timed_end(ctx, s, t0, kNorm, total_elems(segs, n_segs));
-    if (folds) return SDP_OK;
-    return finalize_launch(ctx, plan.tiles * ppt, max_grad_norm, to_host, s);
+    if (run.folds) return SDP_OK;
+    return finalize_launch(ctx, plan.tiles * ppt, max_grad_norm, run.to_host, s);
 }
 
-// folds: the update sums the span pairs itself (there was no finalize).
 int device_update(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool stored_gbar,
-                  const sdp_adamw_params *hp, bool folds, bool to_host, hipStream_t s) {
+                  const sdp_adamw_params *hp, const NormRun &run, hipStream_t s) {
     // a cap on the blocks of a launch: one launch per segment
     if (ctx->update_max_blocks > 0) {
         for (int32_t k = 0; k < n_segs; ++k) {
@@ -464,7 +464,9 @@ int device_update(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t
     sdp::UpdateConsts c{};
     c.ns = ctx->ns;
     fill_consts(hp, c);
-    if (folds) c.sum = norm_sum(ctx, plan.tiles * sdp::norm_pairs_per_tile(R, stored_gbar), hp->max_grad_norm, to_host);
+    c.keep = run.keep & sdp::kKeepUpdate;
+    if (run.folds)
+        c.sum = norm_sum(ctx, plan.tiles * sdp::norm_pairs_per_tile(R, stored_gbar), hp->max_grad_norm, run.to_host);
     hipEvent_t t0 = timed_begin(ctx, s);
     HIP_TRY(sdp::launch_update_segments(R, ks.data(), n_segs, c, ctx->update_lds_pad, ctx->update_segments_lds_pad, s));
     timed_end(ctx, s, t0, kUpdate, total_elems(segs, n_segs));
@@ -935,10 +937,13 @@ int sdp_agg_adam_step(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, con
     SDP_TRY(order_after_last(ctx, s));
     // few pairs: the update sums them (with per-launch timing on, or a cap on
     // a launch's blocks, the finalize stays a launch of its own)
-    const bool folds = plan.tiles * sdp::norm_pairs_per_tile(R, store) <= sdp::kFoldPairs && !ctx->timing &&
-                       ctx->update_max_blocks == 0;
-    SDP_TRY(device_norm(ctx, segs, n_segs, R, plan, store, hp->max_grad_norm, folds, grad_norm_out != nullptr, s));
-    SDP_TRY(device_update(ctx, segs, n_segs, R, plan, store, hp, folds, grad_norm_out != nullptr, s));
+    NormRun run;
+    run.folds = plan.tiles * sdp::norm_pairs_per_tile(R, store) <= sdp::kFoldPairs && !ctx->timing &&
+                ctx->update_max_blocks == 0;
+    run.to_host = grad_norm_out != nullptr;
+    run.keep = sdp::keep_in_cache(R, store, total_elems(segs, n_segs));
+    SDP_TRY(device_norm(ctx, segs, n_segs, R, plan, store, hp->max_grad_norm, run, s));
+    SDP_TRY(device_update(ctx, segs, n_segs, R, plan, store, hp, run, s));
     SDP_TRY(mark_done(ctx, s));
     if (grad_norm_out) {
         NormState st;
@@ -962,7 +967,7 @@ int sdp_grad_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int dev
         SDP_TRY(ensure_partials(ctx, p.tiles * sdp::norm_pairs_per_tile(R, false)));
         hipStream_t s = (hipStream_t)stream;
         SDP_TRY(order_after_last(ctx, s));
-        SDP_TRY(device_norm(ctx, segs, n_segs, R, p, false, 0.0, false, true, s));
+        SDP_TRY(device_norm(ctx, segs, n_segs, R, p, false, 0.0, NormRun(), s));
         SDP_TRY(mark_done(ctx, s));
         SDP_TRY(read_norm(ctx, s, &st));
     } else {
@@ -976,7 +981,7 @@ int sdp_grad_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int dev
         bool used[2] = {false, false};
         MappedSegments mapped;
         int rc = map_segments(ctx, segs, n_segs, R, true, &mapped)
-                     ? device_norm(ctx, mapped.segs.data(), n_segs, R, p, false, 0.0, false, true, ctx->s_comp)
+                     ? device_norm(ctx, mapped.segs.data(), n_segs, R, p, false, 0.0, NormRun(), ctx->s_comp)
                      : stream_norm_phase(ctx, segs, n_segs, R, p, chunks, false, 0.0, used);
         if (rc == SDP_OK) rc = read_norm(ctx, ctx->s_comp, &st);
         int rc2 = sync_streams(ctx);

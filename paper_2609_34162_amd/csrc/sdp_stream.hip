@@ -345,7 +345,7 @@ int sdp_stream_step(sdp_ctx *ctx, const sdp_segment *host_segs, int32_t n_segs, 
     SDP_TRY(order_after_last(ctx, ctx->s_copy));
     SDP_TRY(order_after_last(ctx, ctx->s_comp));
     bool used[2] = {false, false};
-    int rc = direct ? device_norm(ctx, mapped.segs.data(), n_segs, R, plan, store, hp->max_grad_norm, false, true, ctx->s_comp)
+    int rc = direct ? device_norm(ctx, mapped.segs.data(), n_segs, R, plan, store, hp->max_grad_norm, NormRun(), ctx->s_comp)
                     : stream_norm_phase(ctx, host_segs, n_segs, R, plan, norm_chunks, store, hp->max_grad_norm, used);
     NormState st{};
     if (rc == SDP_OK) rc = read_norm(ctx, ctx->s_comp, &st);

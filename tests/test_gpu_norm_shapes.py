@@ -106,3 +106,24 @@ def test_pair_counts_at_the_finalizes_edges(sdp, R, n):
         check_state(dev2.host(), ref)
     finally:
         sdp.sdp_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("R,sizes", [(16, [3125003]), (16, [3124997]), (16, [2000005, 1200003, 4099]), (1, [5, 70001])])
+def test_calls_around_the_cache_rule(sdp, R, sizes):
+    """The update re-reads gradients through the cache up to 50e6 / R elements
+    and with the non-temporal hint above: both kernels, for one segment and for
+    several, give the oracle's states."""
+    log(f"cache rule R={R} sizes={sizes}")
+    masters, grads = rand_inputs(sizes, R, 1, seed=sum(sizes) % 1000)
+    hs, ho = hp_pair(sdp, lr=1e-3, weight_decay=0.02, max_grad_norm=0.05, step=2)
+    ref = oracle.State(masters)
+    _, onorm = oracle.step(ref, grads[0], ho)
+    s = torch.cuda.current_stream()
+    ctx = sdp.sdp_ctx_create(0, 0, R, sdp.SDP_FLAG_DEVICE_GBAR_NEVER)
+    try:
+        dev = DevState(masters, R)
+        dev.set_grads(grads[0])
+        assert sdp.sdp_agg_adam_step(ctx, dev.segments(sdp), hs, 0, s, want_norm=True) == onorm
+        check_state(dev.host(), ref)
+    finally:
+        sdp.sdp_ctx_destroy(ctx)

@@ -1,9 +1,9 @@
 // C ABI of libsdp, the host lanes: parameter delivery (sdp_deliver_params,
 // sdp_cast_bf16_host) and the host-update route (sdp_host_update_step,
 // sdp_host_adamw).  In the route the gradients stay in device memory; the
-// GPU computes the norm and, piece by piece, the mean gradient, which the
-// copy stream moves into pinned stage buffers while the host threads run
-// AdamW on the states in host memory.
+// GPU computes the norm and, piece by piece, the mean gradient, which it
+// writes into pinned stage buffers while the host threads run AdamW on the
+// states in host memory.
 #include "sdp_rt.h"
 #include "sdp_schedule.h"
 

@@ -427,8 +427,10 @@ __device__ __forceinline__ void load_stream_v(const uint16_t *p, uint32_t (&w)[V
 
 // A power of two that is at least the square of every value of magnitude
 // below 2^(e - 126), where e is the biased exponent of the largest magnitude
-// among a lane's values (of the gradients, which bound their mean, or of the
-// means).
+// among a lane's means.  (The gradients bound their mean too, and their
+// largest magnitude is at hand for more than two ranks; but where the ranks
+// cancel it lies far above the means, every square falls below the anchor's
+// last bit, and the pair degrades to lo alone, one FP64 sum.)
 __device__ __forceinline__ double square_anchor(uint32_t e) {
     return __hiloint2double((int)((2u * e + 771u) << 20), 0);  // 2^(2e - 252)
 }
@@ -440,7 +442,9 @@ __device__ __forceinline__ double square_anchor(uint32_t e) {
 // s = fma(g, g, hi), error = fma(g, g, -(s - hi)).  Four operations per value
 // where Knuth's TwoSum on the product takes eight.  The anchor leaves hi
 // exactly at the end (hi is a multiple of its last bit).  What is rounded is
-// lo alone, to 2^-53 of itself: below 2^-90 of the largest square for K <= 32.
+// lo alone, to 2^-53 of itself: below 2^-90 of the largest square for K <= 32
+// (the anchor is at most four times that square, or, among subnormals, has a
+// last bit below that of every square).
 template <int K>
 __device__ __forceinline__ void sum_squares(const float *g, uint32_t e, double &hi, double &lo) {
     const double anchor = square_anchor(e);
@@ -499,16 +503,10 @@ __device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, i
         Span sp = span_init();
 #pragma unroll
         for (int j = 0; j < J; ++j) means_of<R, V / 2>(raw[j], m + j * V, sp);
-        uint32_t e;
         bool fast = true;
-        if constexpr (R > 2) {
-            fast = span_exact<R>(sp);
-            e = (uint32_t)(sp.top.x > sp.top.y ? sp.top.x : sp.top.y) >> 7;
-        } else {
-            e = top_exponent<J * V>(m);
-        }
+        if constexpr (R > 2) fast = span_exact<R>(sp);
         double bh, bl;
-        sum_squares<J * V>(m, e, bh, bl);
+        sum_squares<J * V>(m, top_exponent<J * V>(m), bh, bl);
         if (__builtin_expect(fast, 1)) {
             if constexpr (kIters == 1) {
                 hi = bh;

@@ -51,6 +51,44 @@ def test_norm_bits_at_span_edges(sdp, R, store):
         sdp.sdp_ctx_destroy(ctx)
 
 
+@pytest.mark.parametrize("R", [3, 4, 5, 6, 8, 12, 16])
+@pytest.mark.parametrize("below", [20, 24, 28, 32])
+def test_norm_bits_where_ranks_cancel(sdp, R, below):
+    """Two ranks cancel and the others lie `below` binades under them, still
+    inside the fast route's window: the sum of squares keeps its precision
+    relative to the means, not to the gradients, so the pass that stores
+    g_bar, the reading pass and the no-allocation entry point (whose spans and
+    orders differ) all give the oracle's bits."""
+    log(f"norm where ranks cancel R={R} below={below}")
+    n = 65536 + 4099
+    rng = np.random.default_rng(1000 * R + below)
+    masters, _ = rand_inputs([n], R, 1, seed=R)
+    hs, ho = hp_pair(sdp, lr=1e-3, weight_decay=0.02, max_grad_norm=0.05, step=3)
+    s = torch.cuda.current_stream()
+    stored = sdp.sdp_ctx_create(0, 0, R, sdp.SDP_FLAG_DEVICE_GBAR_ALWAYS)
+    reading = sdp.sdp_ctx_create(0, 0, R, sdp.SDP_FLAG_DEVICE_GBAR_NEVER)
+    try:
+        for trial in range(6):
+            big = synth.to_bf16_bits(rng.uniform(1, 2, n).astype(np.float32))
+            gs = [big, big ^ 0x8000] + [synth.to_bf16_bits((rng.standard_normal(n) * 2.0 ** (-below - 5 * (k % 2))
+                                                            ).astype(np.float32)) for k in range(R - 2)]
+            ref = oracle.State(masters)
+            _, onorm = oracle.step(ref, [gs], ho)
+            for ctx in (stored, reading, None):
+                dev = DevState(masters, R)
+                dev.set_grads([gs])
+                if ctx is None:
+                    norm = sdp.sdp_agg_adam_step_noalloc(dev.segments(sdp), hs, s, want_norm=True)
+                else:
+                    norm = sdp.sdp_agg_adam_step(ctx, dev.segments(sdp), hs, 0, s, want_norm=True)
+                    assert sdp.sdp_grad_norm(ctx, dev.segments(sdp), True, 0, s) == onorm, trial
+                assert norm == onorm, (trial, ctx is None, norm, onorm)
+                check_state(dev.host(), ref)
+    finally:
+        sdp.sdp_ctx_destroy(stored)
+        sdp.sdp_ctx_destroy(reading)
+
+
 @pytest.mark.parametrize("R", [1, 3, 4, 8, 16])
 @pytest.mark.parametrize("count", [2, 19, 33, 64])
 def test_many_segments(sdp, R, count):

@@ -252,7 +252,10 @@ SDP_API int sdp_agg_adam_step_noalloc(const sdp_segment *segs, int32_t n_segs, c
  * at most the context's max_chunk_elems, and n_ranks <= its max_ranks.
  * Pinned memory that the device has mapped (sdp_host_alloc's, hipHostMalloc's)
  * is used where it is: the kernels read and write it over the link, with no
- * copies, and hold compute units while they wait for it.  Otherwise -- staged,
+ * copies, from at most 28 blocks of 256 threads, so that the compute units stay
+ * free for other streams (work on a stream that shares the context's hardware
+ * queue waits for the phase to end, as it does behind the copies).  Otherwise
+ * -- staged,
  * with SDP_FLAG_STREAM_HOST_CAST, with a debug flag, with no mapping, or with
  * the environment variable SDP_STREAM_DIRECT set to 0 or one of the copies'
  * own set, as read at context creation -- the chunks are copied through the

@@ -130,6 +130,7 @@ constexpr int kTile = SDP_NORM_TILE;
 template <int R, bool STORE>
 struct NormShape {
     static constexpr bool kWaveBlocks = STORE && R > 4;
+    static constexpr bool kOneWaveOfBlock = false;  // the whole block works on a span
     static constexpr int kThreads = kWaveBlocks ? 64 : 256;
     static constexpr int kVec = R == 1 && !STORE ? 8 : 4;
     static constexpr int kBatch = STORE ? 1 : R == 1 ? 4 : 2;
@@ -140,6 +141,38 @@ constexpr int norm_pairs_per_tile(int R, bool store) {
     return kTile / (store ? (R > 4 ? NormShape<5, true>::kSpan : NormShape<1, true>::kSpan)
                           : (R == 1 ? NormShape<1, false>::kSpan : NormShape<2, false>::kSpan));
 }
+// Kernels over host memory (streamed mode without copies): as many blocks of
+// kHostThreads as have kHostNormBytes or kHostUpdateBytes of loads on their way
+// over the link together, in whatever number of ranks and lanes.  Enough of
+// them fill the link, and it is bytes that count: some more are 5% slower, and
+// many more, at the rate of these again, hold up the chip's other memory
+// traffic.  ms over 33.6M elements, R = 4, at 150 / 200 / 240 / 280 / 300 / 320
+// / 350 / 450 / 900 KB, the norm pass: 4.73 / 4.69 / 4.69 / 4.67 / 4.67 / 4.71 /
+// 4.89 / 4.97 / 4.67 (R = 16 24.3 / 18.9 / 18.8 / 18.7 / 18.8 / 18.8 / 18.7 /
+// 19.0 / 18.9); at 130 / 160 / 200 / 222 / 235 / 250 / 350 / 500 / 800 KB, the
+// update: 10.3 / 9.34 / 9.24 / 9.16 / 9.16 / 9.62 / 9.84 / 9.29 / 9.24.  (The same
+// waves in blocks of 64 or 512 threads: the update 4 to 9% slower.)
+// A step of 50.3M elements, R = 4, takes 20.7 ms; beside it, a 4096^3 BF16
+// product on another stream (0.14 ms alone) takes 0.23 ms at the median and 0.29
+// at most.  With one-wave blocks for the update (128) and a block for every span
+// of the norm pass: 21.1 ms, 0.32 and 10.4; through copies: 25.2, 0.15 and 4.3.
+constexpr int kHostThreads = 256;
+constexpr int kHostNormBytes = 290000;
+constexpr int kHostUpdateBytes = 230000;
+constexpr int host_blocks(int bytes, int lane_bytes) {
+    return bytes / (lane_bytes * kHostThreads) > 1 ? bytes / (lane_bytes * kHostThreads) : 1;
+}
+// The norm pass there: the spans of NormShape, one wave to a span, with batches
+// of about 64 to 128 bytes of loads per lane, so that few waves fill the link.
+template <int R, bool STORE>
+struct HostNormShape {
+    static constexpr bool kOneWaveOfBlock = true;
+    static constexpr int kThreads = 64;
+    static constexpr int kSpan = NormShape<R, STORE>::kSpan;
+    static constexpr int kVec = NormShape<R, STORE>::kVec;
+    static constexpr int kBatch = kSpan == 256 ? 1 : kVec == 8 ? 4 : R == 1 ? 8 : R <= 3 ? 4 : R <= 8 ? 2 : 1;
+    static constexpr int kBlocks = host_blocks(kHostNormBytes, 2 * R * kVec * kBatch);
+};
 // The finalize: blocks of kFinalizeThreads merge runs of a multiple of kMergeRun
 // pairs each, and the last block to arrive merges their results, so that it is
 // one launch at any size: 4.7 us where two launches took 9 (47,104 pairs).  At
@@ -204,6 +237,9 @@ hipError_t launch_norm_partials(int R, const NormArgs &a, int store_lds_pad, hip
 // one's.
 hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *partials, NormState *ns, int keep,
                                 int store_lds_pad, hipStream_t s);
+// The same with the gradients in host memory, as the device sees them.
+hipError_t launch_norm_segments_host(int R, const Segment *segs, int n, double *partials, NormState *ns,
+                                     hipStream_t s);
 // The update of n segments (all from gbar or none), likewise.
 // lds_pad: for one segment, segments_lds_pad: for several.
 hipError_t launch_update_segments(int R, const Segment *segs, int n, const UpdateConsts &c, int lds_pad,
@@ -211,6 +247,8 @@ hipError_t launch_update_segments(int R, const Segment *segs, int n, const Updat
 // merged: room for kMaxMergeBlocks pairs (used when n_pairs > kMergeRun).
 hipError_t launch_norm_finalize(const NormSum &sum, double *merged, hipStream_t s);
 hipError_t launch_update(int R, UpdateArgs a, int max_blocks, int lds_pad, hipStream_t s);
+// The states, and the gradients unless gbar is set, in host memory.
+hipError_t launch_update_host(int R, const UpdateArgs &a, hipStream_t s);
 // out: pinned host memory as the device sees it.
 hipError_t launch_gbar_out(int R, const GbarArgs &a, int max_blocks, hipStream_t s);
 hipError_t launch_update_pattern(int R, const UpdateArgs &a, int lds_pad, hipStream_t s);

@@ -15,6 +15,8 @@
 // in FP64 registers, each output rounded once to FP32, BF16 from the FP32.
 #include "sdp_internal.h"
 
+#include <algorithm>
+
 namespace sdp {
 namespace {
 
@@ -469,12 +471,14 @@ __device__ __forceinline__ uint32_t top_exponent(const float *g) {
     return m >> 24;
 }
 
-// The pair of span `blk` of the n-element segment g, and its g_bar if STORE.
-// Valid in thread 0.
+// The pair of span `blk` of the n-element segment g, and its g_bar if STORE,
+// by the T threads of a block, or by one wave of it.  Valid in the first of
+// them.
 template <int R, bool STORE, bool KEEP, class S>
 __device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, int64_t blk, float *gbar, double &hi,
                                           double &lo) {
     constexpr int V = S::kVec, T = S::kThreads, J = S::kBatch;
+    const uint32_t lane = S::kOneWaveOfBlock ? threadIdx.x & 63 : threadIdx.x;  // of the span's T
     constexpr int kIters = S::kSpan / (V * T * J);
     static_assert(kIters * V * T * J == S::kSpan, "span must split evenly over the lanes");
     static_assert(kIters <= 32, "one bit per batch of a lane");
@@ -488,7 +492,7 @@ __device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, i
         uint32_t raw[J][R][V / 2];
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            const uint32_t q = (uint32_t)(it * J + j) * T + threadIdx.x;
+            const uint32_t q = (uint32_t)(it * J + j) * T + lane;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (q < groups) {
@@ -517,7 +521,7 @@ __device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, i
             if constexpr (STORE) {
 #pragma unroll
                 for (int j = 0; j < J; ++j) {
-                    const uint32_t q = (uint32_t)(it * J + j) * T + threadIdx.x;
+                    const uint32_t q = (uint32_t)(it * J + j) * T + lane;
                     if (q < groups) {
 #pragma unroll
                         for (int h = 0; h < V / 4; ++h) {
@@ -542,7 +546,7 @@ __device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, i
             wide &= wide - 1;
 #pragma unroll 1
             for (int j = 0; j < J * V / 4; ++j) {
-                const uint32_t q = (uint32_t)(it * J + j / (V / 4)) * T + threadIdx.x;
+                const uint32_t q = (uint32_t)(it * J + j / (V / 4)) * T + lane;
                 if (q >= groups) continue;
                 const int64_t e0 = span0 + q * V + 4 * (j % (V / 4));
                 const float4 t = mean_wide_at4<R>(g, e0);
@@ -555,7 +559,7 @@ __device__ __forceinline__ void norm_span(const uint16_t *const *g, int64_t n, i
         }
     }
     // the segment's ragged tail of fewer than V elements, by one lane of its span
-    if (threadIdx.x == 0 && left > 0 && left < S::kSpan) {
+    if (lane == 0 && left > 0 && left < S::kSpan) {
         for (int64_t i = span0 + (int64_t)groups * V; i < n; ++i) {
             const float t = mean1<R>(g, i);
             dd_add(hi, lo, (double)t * (double)t);
@@ -641,6 +645,35 @@ __global__ __launch_bounds__((NormShape<R, WRITE_GBAR>::kThreads)) void k_norm_s
         partials[2 * (int64_t)blockIdx.x] = hi;
         partials[2 * (int64_t)blockIdx.x + 1] = lo;
         if (blockIdx.x == 0) ns->arrived = 0;
+    }
+}
+
+// The same over host memory (streamed mode without copies): the waves of a few
+// blocks walk the spans, one wave to a span.  Bound by the link.  Blocks for
+// every span under the stored pass's residency pad, which filled the LDS of
+// every compute unit, were no faster and kept the kernels of other streams
+// waiting: a 4096^3 BF16 product of 0.14 ms took up to the whole pass, 14.3 ms
+// at 50M elements and R = 8.
+template <int R, bool WRITE_GBAR>
+__global__ __launch_bounds__(kHostThreads) void k_norm_segments_host(SegTable<R> t, uint32_t spans, double *partials,
+                                                                      NormState *ns) {
+    const uint32_t waves = gridDim.x * (kHostThreads / 64);
+    uint32_t at = blockIdx.x * (kHostThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    // each round of `waves` spans goes round the waves one further on: where the
+    // segments are small, their one span with elements lies at every 16th place
+    for (uint32_t first = 0; first < spans; first += waves, at = at + 1 == waves ? 0 : at + 1) {
+        const uint32_t b = first + at;
+        if (b >= spans) continue;
+        const SegEntry<R> &e = segment_of<R>(t, b);
+        using S = HostNormShape<R, WRITE_GBAR>;
+        double hi = 0.0, lo = 0.0;
+        if ((b - e.first) * S::kSpan < e.n)  // most spans of a small segment's tile lie past its end
+            norm_span<R, WRITE_GBAR, false, S>(e.g, e.n, b - e.first, e.gbar, hi, lo);
+        if ((threadIdx.x & 63) == 0) {
+            partials[2 * (int64_t)b] = hi;
+            partials[2 * (int64_t)b + 1] = lo;
+            if (b == 0) ns->arrived = 0;
+        }
     }
 }
 
@@ -881,6 +914,14 @@ template <int R, bool CACHED>
 __global__ __launch_bounds__(kUpdateThreads) void k_update_keep(UpdateArgs a) {
     update_groups<R, CACHED, false, true>(a.p, a.m, a.v, a.pb, a.g, a.gbar, a.n,
                                           (int64_t)blockIdx.x * kUpdateThreads, a.stride, a);
+}
+
+// The update of a segment in host memory, by the waves of a few blocks.  Bound
+// by the link.
+template <int R, bool CACHED>
+__global__ __launch_bounds__(kHostThreads) void k_update_host(UpdateArgs a) {
+    const int64_t wave = (int64_t)blockIdx.x * (kHostThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    update_groups<R, CACHED, false, false>(a.p, a.m, a.v, a.pb, a.g, a.gbar, a.n, wave * 64, a.stride, a);
 }
 
 // The update of several segments: block b handles the 64 groups from
@@ -1167,6 +1208,44 @@ hipError_t norm_segments_r(const Segment *segs, int n, double *partials, NormSta
     return hipSuccess;
 }
 
+template <int R>
+hipError_t norm_segments_host_r(const Segment *segs, int n, double *partials, NormState *ns, hipStream_t s) {
+    static_assert(HostNormShape<R, true>::kSpan == NormShape<R, true>::kSpan &&
+                      HostNormShape<R, false>::kSpan == NormShape<R, false>::kSpan,
+                  "the pairs of every pass lie alike");
+    const bool store = segs[0].gbar != nullptr;
+    const int ppt = norm_pairs_per_tile(R, store);
+    auto kernel = store ? k_norm_segments_host<R, true> : k_norm_segments_host<R, false>;
+    const int most = store ? HostNormShape<R, true>::kBlocks : HostNormShape<R, false>::kBlocks;
+    for (int k = 0; k < n;) {
+        SegTable<R> t{};
+        int64_t spans = 0;
+        k += fill_table<R>(t, segs + k, n - k, false, [&](int64_t e) { return cdiv(e, kTile) * ppt; }, &spans);
+        const int64_t blocks = std::min<int64_t>(cdiv(spans, kHostThreads / 64), most);
+        hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks), dim3(kHostThreads), 0, s, t, (uint32_t)spans, partials, ns);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        partials += 2 * spans;
+    }
+    return hipSuccess;
+}
+
+template <int R>
+hipError_t update_host_r(UpdateArgs a, hipStream_t s) {
+    // a lane's loads from the host: the three states, and the gradients unless
+    // g_bar is stored.  (Sixteen ranks' gradients take twice the blocks: 33.6M
+    // elements, ms at 230 / 300 / 500 / 1,500 KB: R = 16 31.6 / 28.4 / 25.8 / 25.7,
+    // R = 15 24.9 / 24.5 / 25.4 / 24.5, R = 8 16.5 / 16.6 / 17.6 / 16.5.)
+    const int most = host_blocks(a.gbar || R < 16 ? kHostUpdateBytes : 500000, 3 * 16 + (a.gbar ? 0 : 8 * R));
+    const int64_t blocks = std::min<int64_t>(std::max<int64_t>(cdiv(a.n / kUpdVec, kHostThreads), 1), most);
+    a.stride = blocks * kHostThreads;
+    if (a.gbar)
+        hipLaunchKernelGGL((k_update_host<1, true>), dim3((uint32_t)blocks), dim3(kHostThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_update_host<R, false>), dim3((uint32_t)blocks), dim3(kHostThreads), 0, s, a);
+    return hipGetLastError();
+}
+
 // R ranks, or (CACHED) the stored g_bar, where R = 1 stands for any number.
 template <int R, bool CACHED>
 hipError_t update_segments_r(const Segment *segs, int n, const UpdateConsts &c, int lds_pad, int segments_lds_pad,
@@ -1243,6 +1322,25 @@ hipError_t launch_norm_segments(int R, const Segment *segs, int n, double *parti
                                 int store_lds_pad, hipStream_t s) {
     switch (R) {
 #define CASE(r) case r: return norm_segments_r<r>(segs, n, partials, ns, keep, store_lds_pad, s);
+        SDP_FOR_EACH_R(CASE)
+#undef CASE
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_norm_segments_host(int R, const Segment *segs, int n, double *partials, NormState *ns,
+                                     hipStream_t s) {
+    switch (R) {
+#define CASE(r) case r: return norm_segments_host_r<r>(segs, n, partials, ns, s);
+        SDP_FOR_EACH_R(CASE)
+#undef CASE
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_update_host(int R, const UpdateArgs &a, hipStream_t s) {
+    switch (R) {
+#define CASE(r) case r: return update_host_r<r>(a, s);
         SDP_FOR_EACH_R(CASE)
 #undef CASE
         default: return hipErrorInvalidValue;

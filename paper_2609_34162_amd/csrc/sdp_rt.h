@@ -324,7 +324,7 @@ int norm_launch(sdp_ctx *ctx, int32_t R, const uint16_t *const *g, int64_t n, do
 int finalize_launch(sdp_ctx *ctx, int64_t pairs, double max_grad_norm, bool to_host, hipStream_t s);
 void fill_consts(const sdp_adamw_params *hp, sdp::UpdateConsts &a);
 int update_launch(sdp_ctx *ctx, int32_t R, const sdp_adamw_params *hp, float *p, float *m, float *v, uint16_t *pb,
-                  const uint16_t *const *g, const float *gbar, int64_t n, hipStream_t s, int max_blocks, int lds_pad);
+                  const uint16_t *const *g, const float *gbar, int64_t n, hipStream_t s, bool host_memory);
 int order_after_last(sdp_ctx *ctx, hipStream_t s);
 int mark_done(sdp_ctx *ctx, hipStream_t s);
 int read_norm(sdp_ctx *ctx, hipStream_t s, NormState *out);
@@ -333,6 +333,7 @@ struct NormRun {
     bool folds = false;   // the update sums the span pairs: no finalize
     bool to_host = true;  // the norm state goes to the pinned mirror too, for read_norm
     int keep = 0;         // sdp::keep_in_cache
+    bool host_memory = false;  // the gradients lie in host memory
 };
 int device_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R, const Plan &plan, bool store_gbar,
                 double max_grad_norm, const NormRun &run, hipStream_t s);
@@ -362,12 +363,6 @@ inline bool host_cast(const sdp_ctx *ctx) { return (ctx->flags & SDP_FLAG_STREAM
 size_t off_in_slot(const sdp_ctx *ctx, int sl, const void *p);
 int stream_common_checks(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int64_t chunk, bool grads_only,
                          int32_t *R);
-// Streamed mode's direct path: one-wave blocks of the update (three loads of 16
-// bytes per lane: 393 KB on their way over the link).  ms per
-// step of the Qwen3-8B layer at 16 / 32 / 48 / 64 / 96 / 128 / 192 / 512
-// blocks: 120.7 / 80.6 / 80.0 / 83.8 / 80.1 / 79.8 / 80.7 / 83.2; more of them
-// only disturb the other direction.
-constexpr int kDirectBlocks = 128;
 // Host-update route: 256-thread blocks of the kernel that writes the mean
 // gradient into pinned host memory.  ms per step of the Qwen3-8B layer at 8 /
 // 16 / 32 / 64 / 128 blocks, FP32 mean gradient: 25.8 / 21.2 / 18.2 / 18.2 /

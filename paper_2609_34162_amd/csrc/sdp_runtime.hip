@@ -345,7 +345,7 @@ void fill_consts(const sdp_adamw_params *hp, sdp::UpdateConsts &a) {
 }
 
 int update_launch(sdp_ctx *ctx, int32_t R, const sdp_adamw_params *hp, float *p, float *m, float *v, uint16_t *pb,
-                  const uint16_t *const *g, const float *gbar, int64_t n, hipStream_t s, int max_blocks, int lds_pad) {
+                  const uint16_t *const *g, const float *gbar, int64_t n, hipStream_t s, bool host_memory) {
     sdp::UpdateArgs a{};
     a.p = p;
     a.m = m;
@@ -358,7 +358,8 @@ int update_launch(sdp_ctx *ctx, int32_t R, const sdp_adamw_params *hp, float *p,
     a.ns = ctx->ns;
     fill_consts(hp, a);
     hipEvent_t t0 = timed_begin(ctx, s);
-    HIP_TRY(sdp::launch_update(R, a, max_blocks, lds_pad, s));
+    HIP_TRY(host_memory ? sdp::launch_update_host(R, a, s)
+                        : sdp::launch_update(R, a, ctx->update_max_blocks, ctx->update_lds_pad, s));
     timed_end(ctx, s, t0, kUpdate, n);
     return SDP_OK;
 }
@@ -441,8 +442,10 @@ int device_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t R
     const int ppt = sdp::norm_pairs_per_tile(R, store_gbar);
     const std::vector<sdp::Segment> ks = kernel_segments(ctx, segs, n_segs, plan, store_gbar);
     hipEvent_t t0 = timed_begin(ctx, s);
-    HIP_TRY(sdp::launch_norm_segments(R, ks.data(), n_segs, ctx->partials, ctx->ns, run.keep & sdp::kKeepNorm,
-                                      norm_store_lds_pad(ctx, R), s));
+    HIP_TRY(run.host_memory
+                ? sdp::launch_norm_segments_host(R, ks.data(), n_segs, ctx->partials, ctx->ns, s)
+                : sdp::launch_norm_segments(R, ks.data(), n_segs, ctx->partials, ctx->ns, run.keep & sdp::kKeepNorm,
+                                            norm_store_lds_pad(ctx, R), s));
     timed_end(ctx, s, t0, kNorm, total_elems(segs, n_segs));
     if (run.folds) return SDP_OK;
     return finalize_launch(ctx, plan.tiles * ppt, max_grad_norm, run.to_host, s);
@@ -455,8 +458,7 @@ int device_update(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int32_t
         for (int32_t k = 0; k < n_segs; ++k) {
             const sdp_segment &g = segs[k];
             SDP_TRY(update_launch(ctx, R, hp, g.master, g.exp_avg, g.exp_avg_sq, g.param_bf16, g.grads,
-                                  stored_gbar ? ctx->gbar + plan.gbar_base[k] : nullptr, g.numel, s,
-                                  ctx->update_max_blocks, ctx->update_lds_pad));
+                                  stored_gbar ? ctx->gbar + plan.gbar_base[k] : nullptr, g.numel, s, false));
         }
         return SDP_OK;
     }
@@ -980,8 +982,10 @@ int sdp_grad_norm(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int dev
         SDP_TRY(order_after_last(ctx, ctx->s_comp));
         bool used[2] = {false, false};
         MappedSegments mapped;
+        NormRun run;
+        run.host_memory = true;
         int rc = map_segments(ctx, segs, n_segs, R, true, &mapped)
-                     ? device_norm(ctx, mapped.segs.data(), n_segs, R, p, false, 0.0, NormRun(), ctx->s_comp)
+                     ? device_norm(ctx, mapped.segs.data(), n_segs, R, p, false, 0.0, run, ctx->s_comp)
                      : stream_norm_phase(ctx, segs, n_segs, R, p, chunks, false, 0.0, used);
         if (rc == SDP_OK) rc = read_norm(ctx, ctx->s_comp, &st);
         int rc2 = sync_streams(ctx);

@@ -285,7 +285,7 @@ int stream_update_phase(sdp_ctx *ctx, const sdp_segment *segs, int32_t R, const 
         SDP_TRY(jitter_stream(ctx, ctx->s_comp));
         SDP_TRY(update_launch(ctx, R, hp, slot.p, slot.m, slot.v, slot.pb, gp,
                               stored_gbar ? ctx->gbar + plan.gbar_base[c.seg] + c.off : nullptr, c.len, ctx->s_comp,
-                              ctx->update_max_blocks, ctx->update_lds_pad));
+                              false));
         std::vector<Xfer> out = {{off_in_slot(ctx, sl, slot.p), (char *)(g.master + c.off), f4},
                                  {off_in_slot(ctx, sl, slot.m), (char *)(g.exp_avg + c.off), f4},
                                  {off_in_slot(ctx, sl, slot.v), (char *)(g.exp_avg_sq + c.off), f4}};
@@ -345,7 +345,9 @@ int sdp_stream_step(sdp_ctx *ctx, const sdp_segment *host_segs, int32_t n_segs, 
     SDP_TRY(order_after_last(ctx, ctx->s_copy));
     SDP_TRY(order_after_last(ctx, ctx->s_comp));
     bool used[2] = {false, false};
-    int rc = direct ? device_norm(ctx, mapped.segs.data(), n_segs, R, plan, store, hp->max_grad_norm, NormRun(), ctx->s_comp)
+    NormRun run;
+    run.host_memory = true;
+    int rc = direct ? device_norm(ctx, mapped.segs.data(), n_segs, R, plan, store, hp->max_grad_norm, run, ctx->s_comp)
                     : stream_norm_phase(ctx, host_segs, n_segs, R, plan, norm_chunks, store, hp->max_grad_norm, used);
     NormState st{};
     if (rc == SDP_OK) rc = read_norm(ctx, ctx->s_comp, &st);
@@ -363,8 +365,7 @@ int sdp_stream_step(sdp_ctx *ctx, const sdp_segment *host_segs, int32_t n_segs, 
         for (int32_t k = 0; k < n_segs && rc == SDP_OK; ++k) {
             const sdp_segment &g = mapped.segs[(size_t)k];
             rc = update_launch(ctx, R, hp, g.master, g.exp_avg, g.exp_avg_sq, g.param_bf16, g.grads,
-                               store ? ctx->gbar + plan.gbar_base[(size_t)k] : nullptr, g.numel, ctx->s_comp,
-                               kDirectBlocks, 0);
+                               store ? ctx->gbar + plan.gbar_base[(size_t)k] : nullptr, g.numel, ctx->s_comp, true);
         }
     } else {
         rc = stream_update_phase(ctx, host_segs, R, plan, chunks, store, hp, used, norm_chunks.size());

@@ -255,10 +255,10 @@ SDP_API int sdp_agg_adam_step_noalloc(const sdp_segment *segs, int32_t n_segs, c
  * copies, from at most 28 blocks of 256 threads, so that the compute units stay
  * free for other streams (work on a stream that shares the context's hardware
  * queue waits for the phase to end, as it does behind the copies).  Otherwise
- * -- staged,
- * with SDP_FLAG_STREAM_HOST_CAST, with a debug flag, with no mapping, or with
- * the environment variable SDP_STREAM_DIRECT set to 0 or one of the copies'
- * own set, as read at context creation -- the chunks are copied through the
+ * -- staged, with SDP_FLAG_STREAM_HOST_CAST, with a debug flag, with a buffer
+ * that does not lie in one mapped allocation, or with the environment variable
+ * SDP_STREAM_DIRECT set to 0 or one of the copies' own set, as read at context
+ * creation -- the chunks are copied through the
  * GPU, their transfers overlapping the previous chunk's work, a staging buffer
  * being refilled only after its previous consumer has finished (Design,
  * cross-rank pipelining and chunked overlap within a layer; completion and

@@ -11,8 +11,8 @@
 // event, and leave one direction idle while a pipeline fills and drains.
 //
 // Copies (staged, with the BF16 parameters rounded on the host, with a debug
-// aid for the copies, or where the memory has no mapping): the states move
-// through two device staging slots.  A copy stream carries host-to-device
+// aid for the copies, or where a buffer does not lie in one mapped allocation):
+// the states move through two device staging slots.  A copy stream carries host-to-device
 // copies; a compute
 // stream runs the kernels and the device-to-host copies.  Events h2d_done[s]
 // and slot_free[s] order each slot's reuse: a slot is refilled only after
@@ -21,6 +21,7 @@
 // its copy has landed (chunked overlap within a layer).  Phase 1 streams the
 // gradients for the global norm; phase 2 streams master/m/v through the
 // fused update and back.
+#include "sdp_limits.h"
 #include "sdp_rt.h"
 #include "sdp_schedule.h"
 
@@ -201,20 +202,24 @@ int stream_norm_phase(sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, int
 
 namespace {
 
-// The device's address of pinned host memory [p, p + bytes), if it has one
-// that is contiguous and 16-byte aligned.
-bool map_range(const void *p, size_t bytes, void **out) {
-    const char *end = (const char *)p + bytes - 1;
-    hipPointerAttribute_t first, last;
-    if (hipPointerGetAttributes(&first, p) != hipSuccess || hipPointerGetAttributes(&last, end) != hipSuccess) {
+bool map_pinned(const void *p, size_t bytes, void **out) {
+    auto device_address = [](const void *q) -> void * {
+        hipPointerAttribute_t at;
+        if (hipPointerGetAttributes(&at, q) == hipSuccess) return at.devicePointer;
         (void)hipGetLastError();
-        return false;
-    }
-    if (!first.devicePointer || !last.devicePointer || !aligned(first.devicePointer) ||
-        (char *)last.devicePointer - (char *)first.devicePointer != end - (const char *)p)
-        return false;
-    *out = first.devicePointer;
-    return true;
+        return nullptr;
+    };
+    auto allocation_of = [](void *d, Allocation *a) {
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)d) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        *a = {(const char *)base, size};
+        return true;
+    };
+    return map_range(p, bytes, device_address, allocation_of, out);
 }
 
 }  // namespace
@@ -231,18 +236,18 @@ bool map_segments(const sdp_ctx *ctx, const sdp_segment *segs, int32_t n_segs, i
         const size_t n = (size_t)g.numel;
         void *d = nullptr;
         for (int32_t r = 0; r < R; ++r) {
-            if (!map_range(segs[k].grads[r], 2 * n, &d)) return false;
+            if (!map_pinned(segs[k].grads[r], 2 * n, &d)) return false;
             m->grads[(size_t)k * R + r] = (const uint16_t *)d;
         }
         g.grads = m->grads.data() + (size_t)k * R;
         if (grads_only) continue;
-        if (!map_range(segs[k].master, 4 * n, &d)) return false;
+        if (!map_pinned(segs[k].master, 4 * n, &d)) return false;
         g.master = (float *)d;
-        if (!map_range(segs[k].exp_avg, 4 * n, &d)) return false;
+        if (!map_pinned(segs[k].exp_avg, 4 * n, &d)) return false;
         g.exp_avg = (float *)d;
-        if (!map_range(segs[k].exp_avg_sq, 4 * n, &d)) return false;
+        if (!map_pinned(segs[k].exp_avg_sq, 4 * n, &d)) return false;
         g.exp_avg_sq = (float *)d;
-        if (!map_range(segs[k].param_bf16, 2 * n, &d)) return false;
+        if (!map_pinned(segs[k].param_bf16, 2 * n, &d)) return false;
         g.param_bf16 = (uint16_t *)d;
     }
     return true;

@@ -62,6 +62,31 @@ def test_direct_equals_copies_and_device(sdp, R, never, monkeypatch):
         assert states_equal(got, base), (direct, chunk)
 
 
+def test_pinned_memory_takes_the_direct_path(sdp, monkeypatch):
+    """sdp_host_alloc's memory is known to the runtime as one allocation, so
+    the direct path takes it: one launch of each kernel, where copies make one
+    per chunk."""
+    n, R = 3 * TILE + 5, 2
+    masters, grads = rand_inputs([n], R, 1, seed=9)
+    st = HostState(sdp, masters, R)
+    st.set_grads(grads[0])
+    launches = []
+    try:
+        for direct in ("1", "0"):
+            monkeypatch.setenv("SDP_STREAM_DIRECT", direct)
+            c = sdp.sdp_ctx_create(0, TILE, R, 0)
+            try:
+                sdp.sdp_ctx_set_timing(c, True)
+                sdp.sdp_stream_step(c, st.segments(), sdp.make_params(step=1), TILE)
+                t = sdp.sdp_ctx_get_timing(c)
+                launches.append((t.norm_launches, t.update_launches))
+            finally:
+                sdp.sdp_ctx_destroy(c)
+    finally:
+        st.close()
+    assert launches[0] == (1, 1) and launches[1][1] == 4, launches
+
+
 def test_direct_non_finite_leaves_states(sdp):
     n, R = TILE + 9, 3
     masters, grads = rand_inputs([n], R, 1, seed=5)

@@ -17,6 +17,8 @@
 
 #include <algorithm>
 
+#include "sdp_limits.h"
+
 namespace sdp {
 namespace {
 
@@ -1145,17 +1147,16 @@ int64_t update_blocks(int64_t n) {
     return b < 1 ? 1 : b;
 }
 
-constexpr int64_t kMaxGrid = 0x7fffffff;
-
-// Fills `t` from segs[0 .. n): as many segments as fit the table and the
-// grid; returns how many, and the blocks they need.
+// Fills `t` from segs[0 .. n): as many segments as fit the table and have at
+// most max_blocks blocks; returns how many, and the blocks they need.
 template <int R, class F>
-int fill_table(SegTable<R> &t, const Segment *segs, int n, bool cached_only, F blocks_of, int64_t *blocks) {
-    int k = 0;
+int fill_table(SegTable<R> &t, const Segment *segs, int n, bool cached_only, int64_t max_blocks, F blocks_of,
+               int64_t *blocks) {
+    const int fit = sdprt::segments_that_fit(n, SegTable<R>::kSegs, max_blocks,
+                                             [&](int k) { return blocks_of(segs[k].n); });
     *blocks = 0;
-    for (; k < n && k < SegTable<R>::kSegs; ++k) {
+    for (int k = 0; k < fit; ++k) {
         const int64_t b = blocks_of(segs[k].n);
-        if (k > 0 && *blocks + b > kMaxGrid) break;
         SegEntry<R> &e = t.seg[k];
         e.p = segs[k].p;
         e.m = segs[k].m;
@@ -1173,7 +1174,7 @@ int fill_table(SegTable<R> &t, const Segment *segs, int n, bool cached_only, F b
         while (t.seg[at].end <= (int64_t)run << t.shift) ++at;
         t.map[run / 4] |= (uint32_t)at << (run % 4 * 8);
     }
-    return k;
+    return fit;
 }
 
 template <int R>
@@ -1194,8 +1195,10 @@ hipError_t norm_segments_r(const Segment *segs, int n, double *partials, NormSta
         }
         SegTable<R> t{};
         int64_t blocks = 0;
-        const int done = fill_table<R>(t, segs + k, n - k, false, [&](int64_t e) { return cdiv(e, kTile) * ppt; }, &blocks);
-        const dim3 grid((uint32_t)blocks), block(store ? NormShape<R, true>::kThreads : NormShape<R, false>::kThreads);
+        const int threads = store ? NormShape<R, true>::kThreads : NormShape<R, false>::kThreads;
+        const int done = fill_table<R>(t, segs + k, n - k, false, sdprt::launch_blocks(threads),
+                                       [&](int64_t e) { return cdiv(e, kTile) * ppt; }, &blocks);
+        const dim3 grid((uint32_t)blocks), block(threads);
         const int lds_pad = store ? store_lds_pad : 0;
         auto kernel = store ? (keep ? k_norm_segments<R, true, true> : k_norm_segments<R, true, false>)
                             : (keep ? k_norm_segments<R, false, true> : k_norm_segments<R, false, false>);
@@ -1220,7 +1223,9 @@ hipError_t norm_segments_host_r(const Segment *segs, int n, double *partials, No
     for (int k = 0; k < n;) {
         SegTable<R> t{};
         int64_t spans = 0;
-        k += fill_table<R>(t, segs + k, n - k, false, [&](int64_t e) { return cdiv(e, kTile) * ppt; }, &spans);
+        // the kernel counts spans in 32 bits
+        k += fill_table<R>(t, segs + k, n - k, false, INT32_MAX, [&](int64_t e) { return cdiv(e, kTile) * ppt; }, &spans);
+        if (spans > INT32_MAX) return hipErrorInvalidConfiguration;
         const int64_t blocks = std::min<int64_t>(cdiv(spans, kHostThreads / 64), most);
         hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks), dim3(kHostThreads), 0, s, t, (uint32_t)spans, partials, ns);
         const hipError_t e = hipGetLastError();
@@ -1266,7 +1271,8 @@ hipError_t update_segments_r(const Segment *segs, int n, const UpdateConsts &c, 
         }
         SegTable<R> t{};
         int64_t blocks = 0;
-        const int done = fill_table<R>(t, segs + k, n - k, CACHED, update_blocks, &blocks);
+        const int done = fill_table<R>(t, segs + k, n - k, CACHED, sdprt::launch_blocks(kUpdateThreads), update_blocks,
+                                       &blocks);
         // a call small enough to fold keeps its lines too
         const bool fold = c.sum.n_pairs > 0;
         auto kernel = fold     ? k_update_segments<R, CACHED, true, true>

@@ -7,6 +7,25 @@
 
 namespace sdprt {
 
+// Blocks of `threads` threads that one launch may have: the runtime refuses
+// 2^32 threads or more in a dimension.
+constexpr int64_t launch_blocks(int threads) { return (int64_t)0xffffffff / threads; }
+
+// How many of `n` segments one launch takes: at most max_segs, and only so many
+// that their blocks (blocks_of(k)) together stay within max_blocks; the first in
+// any case.
+template <class BlocksOf>
+int segments_that_fit(int n, int max_segs, int64_t max_blocks, BlocksOf blocks_of) {
+    int k = 0;
+    int64_t blocks = 0;
+    for (; k < n && k < max_segs; ++k) {
+        const int64_t b = blocks_of(k);
+        if (k > 0 && b > max_blocks - blocks) break;
+        blocks += b;
+    }
+    return k;
+}
+
 // An allocation as the device addresses it.
 struct Allocation {
     const char *base;

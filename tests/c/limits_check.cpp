@@ -1,6 +1,7 @@
 // Checks sdp_limits.h without a device; prints "ok" or exits 1.
 #include <cstdio>
 #include <cstdlib>
+#include <initializer_list>
 
 #include "sdp_limits.h"
 
@@ -57,7 +58,27 @@ static void check_map(uintptr_t shift) {
     CHECK(!map_range(at(0x10000), 16, device_address, unknown, &out));
 }
 
+static void check_segments() {
+    // 2^32 threads are too many, one block less is not
+    CHECK(launch_blocks(64) * 64 < (int64_t)1 << 32 && (launch_blocks(64) + 1) * 64 >= (int64_t)1 << 32);
+    CHECK(launch_blocks(256) * 256 < (int64_t)1 << 32 && (launch_blocks(256) + 1) * 256 >= (int64_t)1 << 32);
+    auto fit = [](int n, int max_segs, int64_t most, std::initializer_list<int64_t> blocks) {
+        return segments_that_fit(n, max_segs, most, [&](int k) { return blocks.begin()[k]; });
+    };
+    // three segments of 1.9e9 elements: 30M one-wave blocks each, in two launches
+    const int64_t b = 30000000;
+    CHECK(fit(3, 32, launch_blocks(64), {b, b, b}) == 2);
+    CHECK(fit(2, 32, launch_blocks(64), {launch_blocks(64) - 1, 1}) == 2);
+    CHECK(fit(2, 32, launch_blocks(64), {launch_blocks(64), 1}) == 1);
+    CHECK(fit(2, 32, launch_blocks(256), {launch_blocks(256) - 5, 6}) == 1);
+    // a segment that is too large by itself is left to the launch to refuse
+    CHECK(fit(2, 32, launch_blocks(64), {launch_blocks(64) + 1, 1}) == 1);
+    CHECK(fit(3, 2, launch_blocks(64), {1, 1, 1}) == 2);
+    CHECK(fit(1, 32, launch_blocks(64), {1}) == 1);
+}
+
 int main() {
+    check_segments();
     check_map(0);
     check_map(0x7000000);
     std::printf("ok\n");

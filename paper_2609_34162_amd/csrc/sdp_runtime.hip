@@ -881,7 +881,9 @@ int sdp_ctx_create(sdp_ctx **out, int device, int64_t max_chunk_elems, int32_t m
         c->copier = new_pool(c, default_host_threads());
         c->staged_copy_threads = default_staged_copy_threads();
     }
-    rc = ensure_partials(c, 65536);
+    // 4,096 tiles (268M elements) of any call, so that a later call of at most
+    // so many never has to wait for the device to make room: 16 MB
+    rc = ensure_partials(c, 4096 * sdp::norm_pairs_per_tile(SDP_MAX_RANKS, true));
     if (rc != SDP_OK) return bail(rc);
 #undef CTX_HIP
     *out = c;

@@ -165,3 +165,31 @@ def test_calls_around_the_cache_rule(sdp, R, sizes):
         check_state(dev.host(), ref)
     finally:
         sdp.sdp_ctx_destroy(ctx)
+
+
+def test_a_call_of_many_small_segments_does_not_wait(sdp):
+    """Room for the span pairs of 4,096 tiles is there from the start, also
+    where g_bar is stored with its 256 pairs per tile: an asynchronous call on
+    many small segments returns while earlier work on the stream still runs."""
+    log("many small segments, no wait")
+    R, big, small, count = 8, 30_000_000, 20_000, 1000
+    p, m, v = (torch.zeros(big, device="cuda") for _ in range(3))
+    pb = torch.zeros(big, dtype=torch.int16, device="cuda")
+    g = [torch.zeros(big, dtype=torch.int16, device="cuda") for _ in range(R)]
+    cut = lambda a, n: (p[a:a + n], m[a:a + n], v[a:a + n], pb[a:a + n], [x[a:a + n] for x in g])
+    hs = sdp.make_params(step=1)
+    s = torch.cuda.current_stream()
+    ctx = sdp.sdp_ctx_create(0, 0, R, 0)
+    try:
+        # the mean gradient's own room grows here
+        sdp.sdp_agg_adam_step(ctx, sdp.segments_from_tensors([cut(0, big)]), hs, 0, s)
+        segs = sdp.segments_from_tensors([cut(k * small, small) for k in range(count)])
+        torch.cuda.synchronize()
+        torch.cuda._sleep(400_000_000)  # a few tenths of a second
+        slept = torch.cuda.Event()
+        slept.record()
+        sdp.sdp_agg_adam_step(ctx, segs, hs, 0, s)
+        assert not slept.query(), "the call waited for the device"
+        torch.cuda.synchronize()
+    finally:
+        sdp.sdp_ctx_destroy(ctx)

@@ -65,7 +65,10 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // remainder s - R q is exact in one fma and q + y (s - R q), rounded once, is
 // the correctly rounded quotient (no underflow here: a nonzero |s| is at
 // least 2^-133).  Three operations instead of the divide sequence's eleven.
-// (q only has to be finite: an infinite s takes mean_of_any.)
+// An infinite s gives NaN where the quotient is infinite.  That happens to
+// lanes whose nonzero values all lie within kExactSpan binades of infinity, and
+// nothing shows it: either mean makes the norm NaN, and a call whose norm is not
+// finite updates nothing and uses no mean.
 template <int R>
 __device__ __forceinline__ float mean_of(double s) {
     constexpr double y = 1.0 / (double)R;

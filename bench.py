@@ -25,13 +25,15 @@ line also carries:
                    (FP32 mean gradient, clip_grad_norm_, fused AdamW, BF16
                    cast) on the same GPU;
   streamed      -- one Qwen3-14B layer (330,311,680 parameters, R = 4) in
-                   pinned host memory, streamed in 32M-element chunks, against
-                   the link bound from the faster of the engine's two copy
-                   paths per direction, measured in the same run (runtime
-                   copies; the library's device-to-host copy kernel), with
-                   the BF16 parameters rounded on the host, the staged mode
-                   on pageable memory, parameter delivery, a chunk sweep
-                   beside the step-time model and the model's chunk;
+                   pinned host memory, which the kernels read and write in
+                   place, against the link bound from the faster of the two
+                   copy paths per direction, measured in the same run (runtime
+                   copies; the library's device-to-host copy kernel); the same
+                   step through copies in 32M-element chunks, with a chunk
+                   sweep beside the step-time model, which describes the
+                   copies, and the model's chunk; the BF16 parameters rounded
+                   on the host, the staged mode on pageable memory, and
+                   parameter delivery;
   host_route    -- the paper's own datapath for the same Qwen3-14B layer:
                    gradients in HBM, states in pageable host memory, the mean
                    gradient copied down (FP32 or BF16) and AdamW on this
@@ -45,6 +47,7 @@ Inputs are generated before the timed region and stay resident; the same
 gradient buffers are reused by every timed step.
 """
 import argparse
+import contextlib
 import hashlib
 import json
 import os
@@ -611,6 +614,20 @@ def link_bound_ms(N, R, link, d2h_per_param=14):
     return 1e3 * (2 * R * N / h2d + max(12 * N / h2d, d2h_per_param * N / d2h, (12 + d2h_per_param) * N / both))
 
 
+@contextlib.contextmanager
+def through_copies():
+    """Contexts created inside move pinned streamed state by copies."""
+    old = os.environ.get("SDP_STREAM_DIRECT")
+    os.environ["SDP_STREAM_DIRECT"] = "0"
+    try:
+        yield
+    finally:
+        if old is None:
+            del os.environ["SDP_STREAM_DIRECT"]
+        else:
+            os.environ["SDP_STREAM_DIRECT"] = old
+
+
 def stream_leg(args, torch, np, synth, sdp, dres):
     w = synth.workload(2)
     N, R, C = w.numel, w.ranks, w.chunk
@@ -655,8 +672,14 @@ def stream_leg(args, torch, np, synth, sdp, dres):
     out = dict(workload=w.name, params=N, ranks=R, chunk_elems=C, ms_per_step=el * 1e3,
                params_per_s=N / el, h2d_gbs=h2d_b * N / el / 1e9, d2h_gbs=d2h_b * N / el / 1e9,
                link_gbs={"h2d": link[0], "d2h": link[1], "bidir": link[2]}, link_probe=link_table,
-               t_link_ms=t_link * 1e3, frac_of_link_bound=t_link / el, model_rates=rate_vals,
-               predicted_ms=sdp.sdp_predict_step(sdp.SDP_SCHED_STREAMED, [N], R, C, 0, rates).predicted_ms)
+               t_link_ms=t_link * 1e3, frac_of_link_bound=t_link / el, model_rates=rate_vals)
+    log("streamed leg: through copies")
+    with through_copies():
+        cctx = sdp.sdp_ctx_create(0, C, R, 0)
+    cel = timed(cctx, segs)
+    sdp.sdp_ctx_destroy(cctx)
+    out["copies"] = dict(chunk_elems=C, ms_per_step=cel * 1e3, params_per_s=N / cel, frac_of_link_bound=t_link / cel,
+                         predicted_ms=sdp.sdp_predict_step(sdp.SDP_SCHED_STREAMED, [N], R, C, 0, rates).predicted_ms)
     # the same step with the BF16 parameters rounded on the host from the
     # returned master: 12 B per element back instead of 14
     log("streamed leg: BF16 parameters rounded on the host")
@@ -669,10 +692,11 @@ def stream_leg(args, torch, np, synth, sdp, dres):
                             predicted_ms=sdp.sdp_predict_step(sdp.SDP_SCHED_STREAMED, [N], R, C,
                                                               sdp.SDP_FLAG_STREAM_HOST_CAST, rates).predicted_ms)
     if not args.no_extra:
-        log("streamed leg: chunk sweep")
+        log("streamed leg: chunk sweep of the copies")
 
         def run_at(c):
-            cctx = sdp.sdp_ctx_create(0, c, R, 0)
+            with through_copies():
+                cctx = sdp.sdp_ctx_create(0, c, R, 0)
             try:
                 sdp.sdp_stream_step(cctx, segs, sdp.make_params(**w.hparams(1)), c)
                 times = []
@@ -683,10 +707,10 @@ def stream_leg(args, torch, np, synth, sdp, dres):
                 return times
             finally:
                 sdp.sdp_ctx_destroy(cctx)
-        out["chunk_sweep"] = chunk_sweep(sdp, sdp.SDP_SCHED_STREAMED, [N], R, rates, run_at)
+        out["copies"]["chunk_sweep"] = chunk_sweep(sdp, sdp.SDP_SCHED_STREAMED, [N], R, rates, run_at)
         # the step at the chunk the library's own tuning picks (sdp_tune_chunk)
-        sw = out["chunk_sweep"]
-        out["tuned"] = dict(chunk_elems=sw["model_pick"], ms_per_step=sw["measured_at_model_pick_ms"],
+        sw = out["copies"]["chunk_sweep"]
+        out["copies"]["tuned"] = dict(chunk_elems=sw["model_pick"], ms_per_step=sw["measured_at_model_pick_ms"],
                             params_per_s=N / (sw["measured_at_model_pick_ms"] / 1e3),
                             frac_of_link_bound=t_link * 1e3 / sw["measured_at_model_pick_ms"])
         # the same step with the states in pageable memory, through the staged mode

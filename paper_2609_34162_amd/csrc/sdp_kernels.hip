@@ -631,6 +631,11 @@ struct SegTable {
     SegEntry<R> seg[kSegs];
 };
 
+// With the largest arguments beside it (the update's), within the 4 KiB that
+// segs_per_launch plans for.
+template <int R>
+constexpr bool kTableFits = sizeof(SegTable<R>) + sizeof(UpdateConsts) <= 4096;
+
 template <int R>
 __device__ __forceinline__ const SegEntry<R> &segment_of(const SegTable<R> &t, uint32_t b) {
     const uint32_t run = b >> t.shift;
@@ -1157,6 +1162,7 @@ int fill_table(SegTable<R> &t, const Segment *segs, int n, bool cached_only, int
                int64_t *blocks) {
     const int fit = sdprt::segments_that_fit(n, SegTable<R>::kSegs, max_blocks,
                                              [&](int k) { return blocks_of(segs[k].n); });
+    static_assert(kTableFits<R>, "the kernel arguments of a launch over several segments");
     *blocks = 0;
     for (int k = 0; k < fit; ++k) {
         const int64_t b = blocks_of(segs[k].n);

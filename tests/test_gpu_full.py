@@ -208,10 +208,11 @@ def test_qwen3_14b_layer_device_equals_streamed(sdp):
 
 
 @pytest.mark.timeout(400)
-def test_qwen3_14b_layer_chunk_sizes_agree(sdp):
-    """Chunk invariance at the full layer: streamed mode with chunks of one
-    tile, 16M and 64M elements gives the device mode's bits and norm (the
-    32M chunking is covered above)."""
+def test_qwen3_14b_layer_chunk_sizes_agree(sdp, monkeypatch):
+    """Chunk invariance at the full layer: streamed mode through copies with
+    chunks of one tile, 16M and 64M elements gives the device mode's bits and
+    norm (the 32M chunking is covered above), and so does the path without
+    copies."""
     w = synth.workload(2)
     n, R = w.numel, w.ranks
     master = synth.master(w, 0)
@@ -232,8 +233,9 @@ def test_qwen3_14b_layer_chunk_sizes_agree(sdp):
         dev_to_host(got, dev)
         del dev
         torch.cuda.empty_cache()
-        for chunk in (65536, 1 << 24, 1 << 26):
+        for chunk, direct in ((65536, "0"), (1 << 24, "0"), (1 << 26, "0"), (1 << 24, "1")):
             host = HostState(sdp, [master], R)
+            monkeypatch.setenv("SDP_STREAM_DIRECT", direct)
             ctx = sdp.sdp_ctx_create(0, chunk, R, 0)
             try:
                 for r in range(R):
@@ -241,9 +243,9 @@ def test_qwen3_14b_layer_chunk_sizes_agree(sdp):
                 sn = sdp.sdp_stream_step(ctx, host.segments(), hs, chunk)
                 hstate = oracle.State.__new__(oracle.State)
                 hstate.master, hstate.exp_avg, hstate.exp_avg_sq, hstate.param_bf16 = host.p, host.m, host.v, host.pb
-                assert sn == dn, chunk
-                assert states_equal(got, hstate), f"chunk {chunk} differs from device mode"
-                log(f"  chunk {chunk}: streamed == device, norm {sn:.9g}")
+                assert sn == dn, (chunk, direct)
+                assert states_equal(got, hstate), f"chunk {chunk} (direct {direct}) differs from device mode"
+                log(f"  chunk {chunk} direct {direct}: streamed == device, norm {sn:.9g}")
             finally:
                 sdp.sdp_ctx_destroy(ctx)
                 host.close()

@@ -332,7 +332,7 @@ def test_norm_pattern_probe(sdp, ctx):
 
 
 @pytest.mark.parametrize("chunk_tiles", [1, 2, 4])
-def test_streamed_matches_oracle_and_device(sdp, ctx, ctx_poison, ctx_nostore, chunk_tiles):
+def test_streamed_matches_oracle_and_device(sdp, ctx, ctx_poison, ctx_nostore, chunk_tiles, monkeypatch):
     sizes = [3 * TILE + 5, 1, 70000]
     R = 3
     steps = 2
@@ -349,7 +349,10 @@ def test_streamed_matches_oracle_and_device(sdp, ctx, ctx_poison, ctx_nostore, c
         dev_states.append(dev.host())
         ref_states.append(ref.copy())
         norms.append(dnorm)
-    for c in (ctx_poison, ctx_nostore):
+    # poisoned slots (copies), gradients read twice without copies, and the same through copies
+    monkeypatch.setenv("SDP_STREAM_DIRECT", "0")
+    copies = sdp.sdp_ctx_create(0, 4 * TILE, 16, sdp.SDP_FLAG_DEVICE_GBAR_NEVER | sdp.SDP_FLAG_STREAM_GBAR_NEVER)
+    for c in (ctx_poison, ctx_nostore, copies):
         host = HostState(sdp, masters, R)
         try:
             for t in range(steps):
@@ -361,6 +364,7 @@ def test_streamed_matches_oracle_and_device(sdp, ctx, ctx_poison, ctx_nostore, c
                 assert states_equal(got, dev_states[t]), "streamed differs from device mode"
         finally:
             host.close()
+    sdp.sdp_ctx_destroy(copies)
 
 
 @pytest.mark.parametrize("R", [1, 5, 8, 16])

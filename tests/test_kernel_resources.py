@@ -5,8 +5,11 @@ Every kernel must run without scratch memory: a call stack or a spill puts
 the kernel's waves on scratch, which caps the waves in flight, and such a
 build of the norm pass and the fused update ran three to four times slower.
 The norm passes of the workloads' rank counts must keep full occupancy
-(8 waves per SIMD); the fused update runs under a residency cap of 10
-one-wave blocks per compute unit, so its limit is 4 waves per SIMD.
+(8 waves per SIMD), for one segment and for several, with and without the
+non-temporal hint; the fused update runs under a residency cap of 11 one-wave
+blocks per compute unit (12 for several segments), so its limit is 4 waves per
+SIMD, also where it sums the span pairs itself.  The kernels over host memory
+run one block or two to a compute unit and must fit 4 waves per SIMD.
 """
 import os
 import re
@@ -49,14 +52,36 @@ def test_no_kernel_uses_scratch(report):
     assert not bad, f"kernels with scratch: {bad}"
 
 
+def occupancy(report, kernel, *params):
+    """The occupancy of the instance of `kernel` with these template
+    parameters (the rank count first)."""
+    args = f"Li{int(params[0])}E" + "".join(f"Lb{int(p)}E" for p in params[1:])
+    found = [v["Occupancy"] for k, v in report.items()
+             if k.startswith(f"_ZN3sdp12_GLOBAL__N_1{len(kernel)}{kernel}I{args}E")]
+    assert len(found) == 1, (kernel, params, found)
+    return found[0]
+
+
 @pytest.mark.parametrize("R", [1, 2, 4, 8])
 @pytest.mark.parametrize("store", [0, 1])
 def test_norm_pass_full_occupancy(report, R, store):
-    name = f"_ZN3sdp12_GLOBAL__N_115k_norm_partialsILi{R}ELb{store}EEEvNS_8NormArgsE"
-    assert report[name]["Occupancy"] == 8, report[name]
+    assert occupancy(report, "k_norm_partials", R, store) == 8
+    assert occupancy(report, "k_norm_partials_keep", R, store) == 8
+    for keep in (0, 1):
+        assert occupancy(report, "k_norm_segments", R, store, keep) == 8
 
 
-@pytest.mark.parametrize("R,cached", [(1, 1), (2, 0), (4, 0), (8, 0)])
+@pytest.mark.parametrize("R,cached", [(1, 1), (1, 0), (2, 0), (4, 0), (8, 0), (16, 0)])
 def test_update_fits_its_residency_cap(report, R, cached):
-    name = f"_ZN3sdp12_GLOBAL__N_18k_updateILi{R}ELb{cached}EEEvNS_10UpdateArgsE"
-    assert report[name]["Occupancy"] >= 4, report[name]
+    assert occupancy(report, "k_update", R, cached) >= 4
+    assert occupancy(report, "k_update_keep", R, cached) >= 4
+    for fold, keep in ((0, 0), (0, 1), (1, 1)):
+        assert occupancy(report, "k_update_segments", R, cached, fold, keep) >= 4
+
+
+@pytest.mark.parametrize("R", [1, 2, 4, 8, 16])
+def test_host_memory_kernels_fit_four_waves(report, R):
+    for store in (0, 1):
+        assert occupancy(report, "k_norm_segments_host", R, store) >= 4
+    assert occupancy(report, "k_update_host", R, 0) >= 4
+    assert occupancy(report, "k_update_host", 1, 1) >= 4

@@ -221,9 +221,18 @@ constexpr int kUpdVec = 4;  // fused update: elements per lane (8 B of BF16, 16 
 //           318 / 307 / 331;  768 MB 630 / 630 / 652;  1.6 GB 1316 / 1335 / 1359
 //   R = 2:  64 MB 95.4 / 91.4 / 91.0;  384 MB 516 / 499 / 524;  1.2 GB 1577 / 1580
 //   R = 1:  64 MB 159 / 154 / 153;  384 MB 916 / 898 / 920;  1.2 GB 2807 / 2796
+//   R = 8:  64 MB 46.1 / 46.1 / 45.3;  200 MB 121.5 / 116.5 / 113.6;  768 MB 432 /
+//           426 / 446
+//   R = 16: 64 MB 37.3 / 37.7 / 37.1;  200 MB 99.2 / 94.7 / 91.3;  768 MB 346 / 340 /
+//           362
+// The norm pass's line, 800 MB, is where the gain ends (1 GB, R = 1 to 16: within
+// 0.3% of each other).  The update's, 100 MB, lies below where its reads stop
+// gaining (between 200 and 384 MB).
 // and with stored g_bar (R = 8) by its bytes, hint / stores without / reads too:
 //   64 MB 134.7 / 132.7 / 130.5;  96 MB 195.4 / 192.5 / 189.8;  128 MB 254.8 /
 //   251.3 / 255.4;  256 MB 497 / 490 / 495;  512 MB 1003 / 1013 / 1048
+//   R = 5:  96 MB 175.6 / 172.7 / 168.4;  300 MB 519 / 509 / 536;  512 MB 871 / 870
+//   R = 16: 96 MB 262.9 / 262.0 / 258.5;  300 MB 798 / 792 / 821;  400 MB 1050 / 1061
 constexpr int kKeepNorm = 1, kKeepUpdate = 2;
 constexpr int keep_in_cache(int R, bool store, int64_t elems) {
     return store ? (elems <= 75000000 ? kKeepNorm : 0) | (elems <= 25000000 ? kKeepUpdate : 0)

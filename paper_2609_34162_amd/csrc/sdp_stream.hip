@@ -4,10 +4,10 @@
 // Direct (pinned memory, the default): the kernels read the gradients and the
 // states, and write the results, in host memory itself, through the device's
 // mapping of it.  Bound by the link: the norm pass reads 2R bytes per element,
-// the update reads 12 and writes 14.  Qwen3-8B layer, R = 4: 79.8 ms per step
+// the update reads 12 and writes 14.  Qwen3-8B layer, R = 4: 79.4 ms per step
 // against 84.7 for the copies below at their best chunk and 86.1 at 16M
 // elements, where the link's own rates allow 78.7; 12.6M elements, R = 2, in
-// 1M-element chunks: 4.44 against 5.25 ms.  Copies pay for each command and
+// 1M-element chunks: 4.39 against 5.25 ms.  Copies pay for each command and
 // event, and leave one direction idle while a pipeline fills and drains.
 //
 // Copies (staged, with the BF16 parameters rounded on the host, with a debug

@@ -1,4 +1,5 @@
-"""Every engine under SDP_FLAG_DEBUG_JITTER: random delays of 0-200 us on the
+"""Every engine that copies or hands pieces to the host, under
+SDP_FLAG_DEBUG_JITTER: random delays of 0-200 us on the
 copy stream, the compute stream and the host thread before each of their
 copies, kernels and waits, with the slots poisoned after release where the
 mode has slots.  A missing wait between the streams, or between a stream
